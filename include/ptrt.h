@@ -194,12 +194,18 @@ int ptrt_set_forcing(ptrt_ctx *ctx, int forcing);
  * a solid within one row), or D2Q9 in FP32 or FP64 (with solid nodes or
  * open x: from 2^20 nodes on, while at most 30 % of the rows lie in row
  * chunks with a solid within one row); every other case, and an odd last
- * step, runs one step per pass.  Results are bit-identical either way.
+ * step, runs one step per pass.  With 2, a call of ptrt_step with eight
+ * steps or more on D2Q9 (any storage, PTRT_MODEL_PTRT or _PTRT_EXACT,
+ * PTRT_FORCING_SCHEME2, or PTRT_FORCING_GUO with periodic x) runs all but
+ * its last one or two steps in passes of up to ten on tiles kept in LDS,
+ * where those are the faster ones, and ends with a pass of two steps or a
+ * single step.  Results are bit-identical either way.
  * Allowed at any time (waits for the handle's stream). */
 int ptrt_set_steps_per_pass(ptrt_ctx *ctx, int steps);
 
 /* The most recent kernel pass enqueued by ptrt_step: *steps = the steps it
- * covers (1 or 2; 0 before any step) and *bytes = its algorithmic HBM
+ * covers (1 or 2; 0 before any step; a call that runs in longer passes
+ * ends with one of these) and *bytes = its algorithmic HBM
  * traffic in bytes (one step: 2 Q s per node, plus one mask byte per node
  * with solids; two steps: also 2 Q s per node, the state read once by the
  * first step and written once by the second).  For bandwidth accounting;
@@ -388,8 +394,12 @@ int ptrt_batch_get_plan2(const ptrt_batch *b, int plan_out[5]);
  * duration of the call.  Synchronous. */
 int ptrt_batch_autotune(ptrt_batch *b, int *tile_x, int *tile_y, int *blocks, int *xcd_order);
 
-/* Enqueue n steps over every instance, replayed from captured HIP graphs
- * of ten steps: pairs of steps as two-step passes (below), else one launch
+/* Enqueue n steps over every instance.  With eight steps or more and two
+ * steps per pass (below), all but the last one or two run in passes of up to
+ * ten steps on tiles kept in LDS where those are the faster ones, as
+ * ptrt_set_steps_per_pass describes for a single lattice, and the call ends
+ * with a pass of two steps or a single step.  Otherwise HIP graphs of ten
+ * steps are replayed: pairs of steps as two-step passes, else one launch
  * per step over every instance with the current tile plan.  Asynchronous. */
 int ptrt_batch_step(ptrt_batch *b, int n);
 
@@ -400,8 +410,8 @@ int ptrt_batch_step(ptrt_batch *b, int n);
  * with no solid within one row and one for the others (halfway
  * bounce-back), as ptrt_batch_set_plan2 describes; FP16 / BF16 storage and
  * an odd last step take one step per pass.  Results are bit-identical
- * either way.  The tile plan (set_plan) applies to the one-step launches.
- * Waits for the batch's stream. */
+ * either way.  The tile plan (set_plan) applies to the one-step launches,
+ * the two-step plan to calls of fewer than eight steps.  Waits for the batch's stream. */
 int ptrt_batch_set_steps_per_pass(ptrt_batch *b, int steps);
 
 /* The most recent pass enqueued by ptrt_batch_step: *steps = the steps it

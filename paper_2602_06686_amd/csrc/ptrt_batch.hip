@@ -10,6 +10,8 @@
 // b, b + G, b + 2G, ... of the table (G = grid size).  Each node runs the
 // same pull() and collide() as the single-lattice kernel, so an instance
 // evolves bit for bit like a single lattice with the same parameters.
+// Passes of several steps on tiles in LDS (tile2d.hpp): a task table lists
+// (instance, core of a tile); one workgroup runs one tile.
 // Two steps per pass (FP32 / FP64): a task table lists (instance, strip,
 // chunk of rows) for the single-lattice two-step pass (step2.hpp); one wave
 // runs one task on its instance's block of the state, mask and constants.
@@ -22,17 +24,19 @@
 
 #include "host_common.hpp"
 #include "step_launch.hpp"
+#include "tile_launch.hpp"
 
 using namespace ptrt;
 
-namespace {
+// the tile passes of the 16-bit storage types
+namespace ptrt {
+PTRT_TILE_INSTANCE(_Float16)
+PTRT_TILE_INSTANCE(bf16_t)
+PTRT_TILE_INSTANCE(f16sr_t)
+PTRT_TILE_INSTANCE(bf16sr_t)
+} // namespace ptrt
 
-template <class C>
-struct BInst {
-    long long off, moff, noff; // populations, mask and near-solid row flags
-    Geom g;
-    Coef<D2Q9, C> r;
-};
+namespace {
 
 // Tile table entries are int4 {instance, x0, y0, (nrows << 16) | wpr}.
 // ONEROW (blockDim.y == 1, blockDim.x a multiple of 64): wave w of the
@@ -149,6 +153,10 @@ struct ptrt_batch {
     std::vector<uint8_t> h_near;
     int4 *d_tasks2 = nullptr;
     int n_plain2 = 0, n_masked2 = 0;
+    // passes of several steps: shape and steps of a full pass, task table
+    TilePlan tile;
+    int4 *d_tile_tasks = nullptr;
+    int n_tile_tasks = 0;
     hipStream_t side_stream = nullptr;
     hipEvent_t fork_event = nullptr, join_event = nullptr;
     bool nt = false;
@@ -411,6 +419,49 @@ int build_tasks2(ptrt_batch *b)
     return PTRT_OK;
 }
 
+// The task table of the tile passes: near-equal cores per instance,
+// special where a solid is in reach of the tile.
+int build_tile_tasks(ptrt_batch *b, const uint8_t *mask)
+{
+    std::vector<std::pair<int, int>> sizes;
+    for (const HostInst &h : b->inst) sizes.emplace_back(h.nx, h.ny);
+    const TilePlan p = choose_tile_plan(b->storage, sizes);
+    if (p.shape == TILE_NONE) return PTRT_OK;
+    std::vector<int4> tasks;
+    for (int k = 0; k < b->count; ++k) {
+        const HostInst &h = b->inst[k];
+        const int cw = tile_core(h.nx, p.cw), ch = tile_core(h.ny, p.ch), reach = p.T;
+        SolidReach solids(mask + h.moff, h.nx, h.ny);
+        for (int y0 = 0; y0 < h.ny; y0 += ch) {
+            solids.rows(y0 - reach, y0 + ch + reach);
+            for (int x0 = 0; x0 < h.nx; x0 += cw) {
+                const int cols = std::min(cw, h.nx - x0), rows = std::min(ch, h.ny - y0);
+                const int special = solids.any(x0 - reach, x0 + cols + reach);
+                tasks.push_back(make_int4(k, x0, y0, cols | rows << 15 | special << 30));
+            }
+        }
+    }
+    int4 *fresh = nullptr;
+    const int rc = upload_table(b, tasks, &fresh);
+    if (rc != PTRT_OK) return rc;
+    b->d_tile_tasks = fresh;
+    b->n_tile_tasks = (int)tasks.size();
+    b->tile = p;
+    return PTRT_OK;
+}
+
+void launch_tile_pass(ptrt_batch *b, int T)
+{
+    b->last_steps = T;
+    dispatch_storage(b->storage, false, [&](auto st, auto) -> int {
+        launch_tile_batch<typename decltype(st)::type>(b->buf[b->cur], b->buf[b->cur ^ 1], b->d_mask,
+                                                       b->d_inst, b->d_tile_tasks, b->n_tile_tasks,
+                                                       b->tile.shape, T, b->stream);
+        return PTRT_OK;
+    });
+    b->cur ^= 1;
+}
+
 int capture_graph(ptrt_batch *b, int parity)
 {
     const int saved = b->cur;
@@ -662,6 +713,7 @@ int ptrt_batch_create(int count, const ptrt_instance_desc *desc, int storage, pt
         hipEventCreateWithFlags(&b->join_event, hipEventDisableTiming) != hipSuccess)
         return cleanup(PTRT_EDEVICE, "side stream / events");
     b->h_near = std::move(near);
+    if (build_tile_tasks(b, mask.data()) != PTRT_OK) return cleanup(PTRT_EDEVICE, b->err);
     if (build_tasks2(b) != PTRT_OK) return cleanup(PTRT_EDEVICE, b->err);
     for (int k = 0; k < count; ++k) {
         rc = ptrt_batch_init_equilibrium(b, k, nullptr, nullptr);
@@ -736,6 +788,8 @@ int ptrt_batch_step(ptrt_batch *b, int n)
 {
     if (!b) return PTRT_EINVAL;
     if (n < 0) return bfail(b, PTRT_EINVAL, "negative step count");
+    if (n >= TILE_MIN_STEPS && b->spp == 2 && b->tile.shape != TILE_NONE)
+        n = tile_passes(b->tile, n, [&](int T) { launch_tile_pass(b, T); });
     while (n >= GRAPH_STEPS) {
         if (!b->graph[b->cur]) {
             int rc = capture_graph(b, b->cur);
@@ -1004,6 +1058,7 @@ int ptrt_batch_destroy(ptrt_batch *b)
     if (b->d_inst) hipFree(b->d_inst);
     if (b->d_tiles) hipFree(b->d_tiles);
     if (b->d_tasks2) hipFree(b->d_tasks2);
+    if (b->d_tile_tasks) hipFree(b->d_tile_tasks);
     if (b->d_partials) hipFree(b->d_partials);
     if (b->d_red) hipFree(b->d_red);
     if (b->capture_stream) hipStreamDestroy(b->capture_stream);

@@ -9,8 +9,16 @@
 
 #include "host_common.hpp"
 #include "step_launch.hpp"
+#include "tile_launch.hpp"
 
 using namespace ptrt;
+
+// the tile passes of the 32- and 64-bit storage types (the 16-bit ones are
+// in the batch's translation unit)
+namespace ptrt {
+PTRT_TILE_INSTANCE(double)
+PTRT_TILE_INSTANCE(float)
+} // namespace ptrt
 
 static_assert(FORCE_II == PTRT_FORCING_SCHEME2 && FORCE_II_G == PTRT_FORCING_SCHEME2_G &&
                   FORCE_GUO == PTRT_FORCING_GUO,
@@ -45,6 +53,10 @@ struct ptrt_ctx {
     int4 *d_tasks = nullptr; // plain tasks, then special (masked / open) ones
     int n_plain = 0, n_special = 0;
     long long masked_rows = 0;
+    // D2Q9 passes of several steps on tiles in LDS; d_special: per tile, a
+    // solid or an open x boundary in reach (null without either)
+    TilePlan tile;
+    uint8_t *d_special = nullptr;
     void *buf[2] = {nullptr, nullptr};
     int cur = 0;
     double2 *d_partials = nullptr;
@@ -141,7 +153,7 @@ void release_device(ptrt_ctx *c)
             p = nullptr;
         }
     void **owned[] = {(void **)&c->d_mask, (void **)&c->d_near, (void **)&c->d_tasks,
-                      (void **)&c->d_partials, (void **)&c->d_red};
+                      (void **)&c->d_special, (void **)&c->d_partials, (void **)&c->d_red};
     for (void **p : owned)
         if (*p) {
             (void)hipFree(*p);
@@ -162,6 +174,38 @@ int ensure_allocated(ptrt_ctx *c)
     }
     c->allocated = true;
     return ensure_phi(c, c->forcing);
+}
+
+// The D2Q9 tile plan, and which tiles a solid or an open x boundary is in
+// reach of.
+int plan_tiles(ptrt_ctx *c)
+{
+    TilePlan p = choose_tile_plan(c->storage, {{c->nx, c->ny}});
+    if (p.shape == TILE_NONE) return PTRT_OK;
+    p.cw = tile_core(c->nx, p.cw);
+    p.ch = tile_core(c->ny, p.ch);
+    p.tiles_x = (c->nx + p.cw - 1) / p.cw;
+    p.tiles = p.tiles_x * ((c->ny + p.ch - 1) / p.ch);
+    c->tile = p;
+    if (!c->has_mask && !c->open) return PTRT_OK;
+    std::vector<uint8_t> special(p.tiles, 0);
+    const int reach = p.T; // the region and one node around it
+    if (c->has_mask) {
+        SolidReach solids(c->h_mask.data(), c->nx, c->ny);
+        for (int t = 0; t < p.tiles; ++t) {
+            const int x0 = t % p.tiles_x * p.cw, y0 = t / p.tiles_x * p.ch;
+            if (x0 == 0) solids.rows(y0 - reach, y0 + p.ch + reach);
+            special[t] = solids.any(x0 - reach, x0 + p.cw + reach);
+        }
+    }
+    if (c->open)
+        for (int t = 0; t < p.tiles; ++t) {
+            const int x0 = t % p.tiles_x * p.cw;
+            if (x0 - reach <= 0 || x0 + p.cw + reach >= c->nx) special[t] = 1;
+        }
+    HIPCHK(c, hipMalloc(&c->d_special, special.size()));
+    HIPCHK(c, hipMemcpy(c->d_special, special.data(), special.size(), hipMemcpyHostToDevice));
+    return PTRT_OK;
 }
 
 int allocate_device(ptrt_ctx *c)
@@ -263,6 +307,10 @@ int allocate_device(ptrt_ctx *c)
         plain.insert(plain.end(), special.begin(), special.end());
         HIPCHK(c, hipMalloc(&c->d_tasks, sizeof(int4) * plain.size()));
         HIPCHK(c, hipMemcpy(c->d_tasks, plain.data(), sizeof(int4) * plain.size(), hipMemcpyHostToDevice));
+    }
+    if (c->lattice == PTRT_D2Q9) {
+        const int rc = plan_tiles(c);
+        if (rc != PTRT_OK) return rc;
     }
     const dim3 gg = gather_grid(c, c->nz);
     c->nparts = gg.x * gg.y * gg.z;
@@ -617,9 +665,31 @@ int launch_check(ptrt_ctx *c)
     return PTRT_OK;
 }
 
-// Enqueue n steps: graph replays where captured, else launches.
+// Tile passes cover calls of TILE_MIN_STEPS steps and more of P-TRT on
+// D2Q9 with the default forcing or, on periodic lattices, Scheme I.
+bool tiles_apply(const ptrt_ctx *c, int n)
+{
+    return n >= TILE_MIN_STEPS && c->steps_per_pass == 2 && c->tile.shape != TILE_NONE &&
+           (c->model == MODEL_PTRT || c->model == MODEL_PTRT_EXACT) &&
+           (c->forcing == FORCE_II || (c->forcing == FORCE_GUO && !c->open));
+}
+
+void launch_tile_pass(ptrt_ctx *c, int T)
+{
+    const StepLaunch a = step_args(c, c->stream);
+    dispatch_storage(c->storage, false, [&](auto st, auto) -> int {
+        launch_tile<typename decltype(st)::type>(a, c->tile, c->d_special, T);
+        return PTRT_OK;
+    });
+    c->cur ^= 1;
+    c->last_pass_steps = T;
+    c->last_pass_bytes = ptrt_bytes_per_node(c) * (double)c->N;
+}
+
+// Enqueue n steps: tile passes, graph replays where captured, else launches.
 int advance(ptrt_ctx *c, int n)
 {
+    if (tiles_apply(c, n)) n = tile_passes(c->tile, n, [&](int T) { launch_tile_pass(c, T); });
     if (c->use_graph)
         while (n >= GRAPH_STEPS) {
             if (!c->graph[c->cur]) {
@@ -956,6 +1026,7 @@ int ptrt_destroy(ptrt_ctx *c)
     if (c->d_mask) (void)hipFree(c->d_mask);
     if (c->d_near) (void)hipFree(c->d_near);
     if (c->d_tasks) (void)hipFree(c->d_tasks);
+    if (c->d_special) (void)hipFree(c->d_special);
     for (auto &gx : c->graph)
         if (gx) (void)hipGraphExecDestroy(gx);
     if (c->capture_stream) (void)hipStreamDestroy(c->capture_stream);
