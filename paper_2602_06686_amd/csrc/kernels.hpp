@@ -425,47 +425,58 @@ k_step(const S *__restrict__ src, S *__restrict__ dst, const uint8_t *__restrict
 }
 
 // ---------------------------------------------------------------------------
-// Scatter a full FP64 state f[Q][N] (unshifted) into dst (pre-collision at t).
-template <class L, class S, bool MASK, bool OPEN = false>
+// Kernels between the state and host arrays.  They take nodes n0 ... n0 +
+// count - 1 of the lattice (node = row * nx + x), one per thread, and read or
+// write one chunk buffer in pinned host memory, component-major with stride
+// count: contiguous 8-byte (4-byte) accesses, bound by PCIe (56 GB/s).
+struct NodeRange {
+    unsigned n0, count;
+    int x, y, z;
+    unsigned row, node, at; // node number in the lattice and in the chunk
+    __device__ __forceinline__ bool place(const Geom &g)
+    {
+        at = blockIdx.x * blockDim.x + threadIdx.x;
+        if (at >= count) return false;
+        node = n0 + at;
+        row = node / (unsigned)g.nx;
+        x = (int)(node - row * (unsigned)g.nx);
+        z = (int)(row / (unsigned)g.ny);
+        y = (int)(row - (unsigned)z * (unsigned)g.ny);
+        return true;
+    }
+};
+
+// Scatter a full state f[Q] (pre-collision at t) into dst: FP64 unshifted
+// populations, or FP32 shifted ones (already rounded from FP64).
+template <class L, class S, bool MASK, bool OPEN, class V>
 __global__ void __launch_bounds__(256)
-k_set_state(S *__restrict__ dst, const uint8_t *__restrict__ mask, Geom g, int z0,
-            const double *__restrict__ f, long long fstride)
+k_set_state(S *__restrict__ dst, const uint8_t *__restrict__ mask, Geom g, NodeRange r,
+            const V *__restrict__ f)
 {
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    const int y = blockIdx.y * blockDim.y + threadIdx.y;
-    const int z = blockIdx.z + z0;
-    if (x >= g.nx || y >= g.ny) return;
-    const unsigned node = ((unsigned)z * (unsigned)g.ny + (unsigned)y) * (unsigned)g.nx + (unsigned)x;
-    const unsigned in = node - (unsigned)z0 * (unsigned)g.ny * (unsigned)g.nx;
-    if (MASK && mask[node]) return;
+    if (!r.place(g) || (MASK && mask[r.node])) return;
     double hv[L::Q];
     static_for<L::Q>([&](auto ic) {
         constexpr int i = decltype(ic)::value;
-        hv[i] = f[(long long)i * fstride + in] - L::w(i);
+        const double v = (double)f[(size_t)i * r.count + r.at];
+        hv[i] = sizeof(V) == 8 ? v - L::w(i) : v;
     });
-    scatter<L, S, MASK, OPEN>(dst, mask, g, x, y, z, hv);
+    scatter<L, S, MASK, OPEN>(dst, mask, g, r.x, r.y, r.z, hv);
 }
 
-// Equilibrium initialisation (Eq. feq) in FP64 from rho[N] and u[3][N]
-// (either may be null: rho = 1, u = 0), scattered into dst.
+// Equilibrium initialisation (Eq. feq) in FP64 from rho and u[D] (either may
+// be null: rho = 1, u = 0), scattered into dst.
 template <class L, class S, bool MASK, bool OPEN = false>
 __global__ void __launch_bounds__(256)
-k_init_eq(S *__restrict__ dst, const uint8_t *__restrict__ mask, Geom g, int z0,
-          const double *__restrict__ rho_in, const double *__restrict__ u_in, long long ustride)
+k_init_eq(S *__restrict__ dst, const uint8_t *__restrict__ mask, Geom g, NodeRange r,
+          const double *__restrict__ rho_in, const double *__restrict__ u_in)
 {
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    const int y = blockIdx.y * blockDim.y + threadIdx.y;
-    const int z = blockIdx.z + z0;
-    if (x >= g.nx || y >= g.ny) return;
-    const unsigned node = ((unsigned)z * (unsigned)g.ny + (unsigned)y) * (unsigned)g.nx + (unsigned)x;
-    const unsigned in = node - (unsigned)z0 * (unsigned)g.ny * (unsigned)g.nx;
-    if (MASK && mask[node]) return;
-    const double rho = rho_in ? rho_in[in] : 1.0;
+    if (!r.place(g) || (MASK && mask[r.node])) return;
+    const double rho = rho_in ? rho_in[r.at] : 1.0;
     double ux = 0.0, uy = 0.0, uz = 0.0;
     if (u_in) {
-        ux = u_in[in];
-        uy = u_in[ustride + in];
-        if (L::D == 3) uz = u_in[2 * ustride + in];
+        ux = u_in[r.at];
+        uy = u_in[(size_t)r.count + r.at];
+        if (L::D == 3) uz = u_in[2 * (size_t)r.count + r.at];
     }
     const double uu = ux * ux + uy * uy + uz * uz;
     double hv[L::Q];
@@ -475,65 +486,90 @@ k_init_eq(S *__restrict__ dst, const uint8_t *__restrict__ mask, Geom g, int z0,
         const double poly = 3.0 * eu + 4.5 * eu * eu - 1.5 * uu + 4.5 * eu * (eu * eu - uu);
         hv[i] = L::w(i) * ((rho - 1.0) + rho * poly);
     });
-    scatter<L, S, MASK, OPEN>(dst, mask, g, x, y, z, hv);
+    scatter<L, S, MASK, OPEN>(dst, mask, g, r.x, r.y, r.z, hv);
+}
+
+// Density and velocity (Eq. macro) of FP64 populations; solid nodes zero.
+template <class L>
+__device__ __forceinline__ void macro_f64(const double (&h)[L::Q], double gx, double gy, double gz,
+                                          double &rho, double &ux, double &uy, double &uz)
+{
+    double drho, jx, jy, jz;
+    shifted_moments<L>(h, drho, jx, jy, jz);
+    rho = 1.0 + drho;
+    ux = (jx + 0.5 * rho * gx) / rho;
+    uy = (jy + 0.5 * rho * gy) / rho;
+    uz = (jz + 0.5 * rho * gz) / rho;
+}
+
+// Read the pre-collision state at t: rho and u[D] (either may be null).
+// Solid nodes report zeros.
+template <class L, class S, bool MASK, bool OPEN = false>
+__global__ void __launch_bounds__(256)
+k_read_moments(const S *__restrict__ src, const uint8_t *__restrict__ mask, Geom g, NodeRange r,
+               double gx, double gy, double gz, double *__restrict__ rho_out,
+               double *__restrict__ u_out)
+{
+    if (!r.place(g)) return;
+    double rho = 0.0, ux = 0.0, uy = 0.0, uz = 0.0;
+    if (!(MASK && mask[r.node])) {
+        double h[L::Q];
+        pull<L, S, MASK, OPEN>(src, mask, g, r.x, r.y, r.z, h, [](const S *p) { return load_f64(p); });
+        macro_f64<L>(h, gx, gy, gz, rho, ux, uy, uz);
+    }
+    if (rho_out) rho_out[r.at] = rho;
+    if (u_out) {
+        u_out[r.at] = ux;
+        u_out[(size_t)r.count + r.at] = uy;
+        if (L::D == 3) u_out[2 * (size_t)r.count + r.at] = uz;
+    }
+}
+
+// Read the populations f[Q] at t: FP64 unshifted with zeros at solid nodes,
+// or FP32 shifted (storage of 32 bits and less, whose values it holds
+// exactly; solid nodes hold no meaning).
+template <class L, class S, bool MASK, bool OPEN, class V>
+__global__ void __launch_bounds__(256)
+k_read_state(const S *__restrict__ src, const uint8_t *__restrict__ mask, Geom g, NodeRange r,
+             V *__restrict__ f)
+{
+    static_assert(sizeof(V) == 8 || !OPEN, "open boundaries compute populations in FP64");
+    if (!r.place(g)) return;
+    if (MASK && mask[r.node]) {
+        for (int i = 0; i < L::Q; ++i) f[(size_t)i * r.count + r.at] = V(0);
+        return;
+    }
+    V h[L::Q];
+    pull<L, S, MASK, OPEN>(src, mask, g, r.x, r.y, r.z, h, [](const S *p) { return (V)Codec<S>::load(p); });
+    static_for<L::Q>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        f[(size_t)i * r.count + r.at] = sizeof(V) == 8 ? V(h[i] + L::w(i)) : h[i];
+    });
 }
 
 // ---------------------------------------------------------------------------
-// Gather the pre-collision state at t: any of rho[N], u[3][N], f[Q][N]
-// (unshifted) and per-block (mass, kinetic energy) partials.  Solid nodes
-// report zeros and contribute nothing.
+// Per-block (mass, kinetic energy) partials of the pre-collision state at t.
+// Solid nodes contribute nothing.
 template <class L, class S, bool MASK, bool OPEN = false>
 __global__ void __launch_bounds__(256)
-k_gather(const S *__restrict__ src, const uint8_t *__restrict__ mask, Geom g, int z0, double gx,
-         double gy, double gz, double *__restrict__ rho_out, double *__restrict__ u_out,
-         double *__restrict__ f_out, long long ostride, double2 *__restrict__ partials)
+k_gather(const S *__restrict__ src, const uint8_t *__restrict__ mask, Geom g, double gx, double gy,
+         double gz, double2 *__restrict__ partials)
 {
     const int x = blockIdx.x * blockDim.x + threadIdx.x;
     const int y = blockIdx.y * blockDim.y + threadIdx.y;
-    const int z = blockIdx.z + z0;
-    const bool inside = x < g.nx && y < g.ny;
+    const int z = blockIdx.z;
     const unsigned node = ((unsigned)z * (unsigned)g.ny + (unsigned)y) * (unsigned)g.nx + (unsigned)x;
-    const unsigned on = node - (unsigned)z0 * (unsigned)g.ny * (unsigned)g.nx;
-    const bool fluid = inside && !(MASK && mask[node]);
     double m = 0.0, k = 0.0;
-    if (fluid) {
+    if (x < g.nx && y < g.ny && !(MASK && mask[node])) {
         double h[L::Q];
         pull<L, S, MASK, OPEN>(src, mask, g, x, y, z, h, [](const S *p) { return load_f64(p); });
-        double drho, jx, jy, jz;
-        shifted_moments<L>(h, drho, jx, jy, jz);
-        const double rho = 1.0 + drho;
-        const double ux = (jx + 0.5 * rho * gx) / rho;
-        const double uy = (jy + 0.5 * rho * gy) / rho;
-        const double uz = (jz + 0.5 * rho * gz) / rho;
-        if (rho_out) rho_out[on] = rho;
-        if (u_out) {
-            u_out[on] = ux;
-            u_out[ostride + on] = uy;
-            u_out[2 * ostride + on] = uz;
-        }
-        if (f_out) {
-            static_for<L::Q>([&](auto ic) {
-                constexpr int i = decltype(ic)::value;
-                f_out[(long long)i * ostride + on] = h[i] + L::w(i);
-            });
-        }
+        double rho, ux, uy, uz;
+        macro_f64<L>(h, gx, gy, gz, rho, ux, uy, uz);
         m = rho;
         k = 0.5 * rho * (ux * ux + uy * uy + uz * uz);
-    } else if (inside) {
-        if (rho_out) rho_out[on] = 0.0;
-        if (u_out) {
-            u_out[on] = 0.0;
-            u_out[ostride + on] = 0.0;
-            u_out[2 * ostride + on] = 0.0;
-        }
-        if (f_out) {
-            for (int i = 0; i < L::Q; ++i) f_out[(long long)i * ostride + on] = 0.0;
-        }
     }
-    if (partials) {
-        block_sum2(m, k);
-        if (threadIdx.x == 0 && threadIdx.y == 0) partials[flat_block()] = make_double2(m, k);
-    }
+    block_sum2(m, k);
+    if (threadIdx.x == 0 && threadIdx.y == 0) partials[flat_block()] = make_double2(m, k);
 }
 
 // Sum nparts partials in a fixed order (deterministic) into out[0..1].

@@ -23,6 +23,7 @@
 #include <vector>
 
 #include "host_common.hpp"
+#include "host_stage.hpp"
 #include "step_launch.hpp"
 #include "tile_launch.hpp"
 
@@ -130,6 +131,7 @@ struct HostInst {
 struct ptrt_batch {
     int count = 0, storage = PTRT_F32;
     std::vector<HostInst> inst;
+    std::shared_ptr<HostPool> pool; // host threads and pinned memory of the transfers
     long long total_elems = 0, total_nodes = 0, mask_bytes = 0;
     void *buf[2] = {nullptr, nullptr};
     int cur = 0;
@@ -618,6 +620,12 @@ int ptrt_batch_create(int count, const ptrt_instance_desc *desc, int storage, pt
     if (!b) return PTRT_ENOMEM;
     b->count = count;
     b->storage = storage;
+    b->pool = HostPool::shared();
+    if (!b->pool) {
+        delete b;
+        g_batch_create_error = "out of host memory";
+        return PTRT_ENOMEM;
+    }
     b->inst.resize(count);
     const size_t elem = storage_bytes(storage);
     std::vector<uint8_t> mask, near;
@@ -735,31 +743,46 @@ int ptrt_batch_init_equilibrium(ptrt_batch *b, int k, const double *rho, const d
     int rc = check_instance(b, k);
     if (rc != PTRT_OK) return rc;
     const HostInst &h = b->inst[k];
-    double *d_in = nullptr;
-    BHIPCHK(b, hipMalloc(&d_in, sizeof(double) * 3 * (size_t)h.N));
-    hipError_t e = hipSuccess;
-    if (rho) e = hipMemcpyAsync(d_in, rho, sizeof(double) * h.N, hipMemcpyHostToDevice, b->stream);
-    if (u && e == hipSuccess)
-        e = hipMemcpyAsync(d_in + h.N, u, sizeof(double) * 2 * h.N, hipMemcpyHostToDevice, b->stream);
-    if (e == hipSuccess) {
+    const Geom g = inst_geom(h);
+    const int fields = (rho ? 1 : 0) + (u ? 2 : 0);
+    auto launch = [&](char *buffer, long long n0, long long count) {
+        const double *d_rho = rho ? (const double *)buffer : nullptr;
+        const double *d_u = u ? (const double *)buffer + (rho ? count : 0) : nullptr;
+        NodeRange r{};
+        r.n0 = (unsigned)n0;
+        r.count = (unsigned)count;
         // both buffers hold the same state so that either parity is valid
-        const Geom g = inst_geom(h);
         for (int k2 = 0; k2 < 2; ++k2) {
             void *dst = b->buf[b->cur ^ k2];
-            dispatch(PTRT_D2Q9, b->storage, h.has_mask, [&](auto lt, auto st, auto mk) -> int {
-                using L = typename decltype(lt)::type;
+            dispatch_storage(b->storage, h.has_mask, [&](auto st, auto mk) -> int {
                 using S = typename decltype(st)::type;
-                constexpr bool M = decltype(mk)::value;
-                hipLaunchKernelGGL((k_init_eq<L, S, M>), dim3((h.nx + BLK_X - 1) / BLK_X, (h.ny + BLK_Y - 1) / BLK_Y, 1),
-                                   dim3(BLK_X, BLK_Y, 1), 0, b->stream, (S *)dst + h.off, b->d_mask + h.moff, g,
-                                   0, rho ? d_in : nullptr, u ? d_in + h.N : nullptr, h.N);
+                hipLaunchKernelGGL((k_init_eq<D2Q9, S, decltype(mk)::value>), dim3((unsigned)((count + 255) / 256)),
+                                   dim3(256), 0, b->stream, (S *)dst + h.off, b->d_mask + h.moff, g, r, d_rho,
+                                   d_u);
                 return PTRT_OK;
             });
         }
+    };
+    hipError_t e;
+    if (fields == 0) {
+        launch(nullptr, 0, h.N);
         e = hipGetLastError();
+        if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
+    } else {
+        StageRing ring(b->pool, h.N, fields * sizeof(double), b->stream);
+        e = ring.in(
+            [&](char *buffer, long long n0, long long count, long long a, long long z) {
+                double *to = (double *)buffer;
+                const size_t bytes = (size_t)(z - a) * sizeof(double);
+                if (rho) {
+                    std::memcpy(to + a, rho + n0 + a, bytes);
+                    to += count;
+                }
+                for (int d = 0; u && d < 2; ++d)
+                    std::memcpy(to + d * count + a, u + (size_t)d * h.N + n0 + a, bytes);
+            },
+            launch);
     }
-    if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
-    hipFree(d_in);
     if (e != hipSuccess) return bfail_hip(b, PTRT_EDEVICE, std::string("init: ") + hipGetErrorString(e));
     return PTRT_OK;
 }
@@ -951,52 +974,75 @@ int ptrt_batch_autotune(ptrt_batch *b, int *tx_o, int *ty_o, int *blocks_o, int 
     return rc;
 }
 
-static int batch_download(ptrt_batch *b, int k, double *rho, double *u, double *f)
+int ptrt_batch_moments(ptrt_batch *b, int k, double *rho, double *u)
 {
     int rc = check_instance(b, k);
     if (rc != PTRT_OK) return rc;
     const HostInst &h = b->inst[k];
-    const int per = (rho ? 1 : 0) + (u ? 3 : 0) + (f ? 9 : 0);
-    if (per == 0) return PTRT_OK;
-    double *d_out = nullptr;
-    BHIPCHK(b, hipMalloc(&d_out, sizeof(double) * per * (size_t)h.N));
-    double *d_rho = rho ? d_out : nullptr;
-    double *d_u = u ? d_out + (rho ? h.N : 0) : nullptr;
-    double *d_f = f ? d_out + ((rho ? 1 : 0) + (u ? 3 : 0)) * h.N : nullptr;
+    const int fields = (rho ? 1 : 0) + (u ? 2 : 0);
+    if (fields == 0) return PTRT_OK;
     const Geom g = inst_geom(h);
-    dispatch(PTRT_D2Q9, b->storage, h.has_mask, [&](auto lt, auto st, auto mk) -> int {
-        using L = typename decltype(lt)::type;
-        using S = typename decltype(st)::type;
-        constexpr bool M = decltype(mk)::value;
-        hipLaunchKernelGGL((k_gather<L, S, M>), dim3((h.nx + BLK_X - 1) / BLK_X, (h.ny + BLK_Y - 1) / BLK_Y, 1),
-                           dim3(BLK_X, BLK_Y, 1), 0, b->stream, (const S *)b->buf[b->cur] + h.off,
-                           b->d_mask + h.moff, g, 0, h.force[0], h.force[1], 0.0, d_rho, d_u, d_f, h.N,
-                           (double2 *)nullptr);
-        return PTRT_OK;
-    });
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess && rho)
-        e = hipMemcpyAsync(rho, d_rho, sizeof(double) * h.N, hipMemcpyDeviceToHost, b->stream);
-    if (e == hipSuccess && u)
-        e = hipMemcpyAsync(u, d_u, sizeof(double) * 2 * h.N, hipMemcpyDeviceToHost, b->stream);
-    if (e == hipSuccess && f)
-        e = hipMemcpyAsync(f, d_f, sizeof(double) * 9 * h.N, hipMemcpyDeviceToHost, b->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
-    hipFree(d_out);
+    StageRing ring(b->pool, h.N, fields * sizeof(double), b->stream);
+    const hipError_t e = ring.out(
+        [&](char *buffer, long long n0, long long count) {
+            double *d_rho = rho ? (double *)buffer : nullptr;
+            double *d_u = u ? (double *)buffer + (rho ? count : 0) : nullptr;
+            NodeRange r{};
+            r.n0 = (unsigned)n0;
+            r.count = (unsigned)count;
+            dispatch_storage(b->storage, h.has_mask, [&](auto st, auto mk) -> int {
+                using S = typename decltype(st)::type;
+                hipLaunchKernelGGL((k_read_moments<D2Q9, S, decltype(mk)::value>),
+                                   dim3((unsigned)((count + 255) / 256)), dim3(256), 0, b->stream,
+                                   (const S *)b->buf[b->cur] + h.off, b->d_mask + h.moff, g, r, h.force[0],
+                                   h.force[1], 0.0, d_rho, d_u);
+                return PTRT_OK;
+            });
+        },
+        [&](char *buffer, long long n0, long long count, long long a, long long z) {
+            const double *from = (const double *)buffer;
+            const size_t bytes = (size_t)(z - a) * sizeof(double);
+            if (rho) {
+                std::memcpy(rho + n0 + a, from + a, bytes);
+                from += count;
+            }
+            for (int d = 0; u && d < 2; ++d)
+                std::memcpy(u + (size_t)d * h.N + n0 + a, from + d * count + a, bytes);
+            if (u) std::memset(u + 2 * (size_t)h.N + n0 + a, 0, bytes);
+        });
     if (e != hipSuccess) return bfail_hip(b, PTRT_EDEVICE, std::string("download: ") + hipGetErrorString(e));
-    if (u) std::memset(u + 2 * h.N, 0, sizeof(double) * h.N);
     return PTRT_OK;
-}
-
-int ptrt_batch_moments(ptrt_batch *b, int k, double *rho, double *u)
-{
-    return batch_download(b, k, rho, u, nullptr);
 }
 
 int ptrt_batch_get_populations(ptrt_batch *b, int k, double *f)
 {
     if (!f) return bfail(b, PTRT_EINVAL, "NULL argument");
-    return batch_download(b, k, nullptr, nullptr, f);
+    int rc = check_instance(b, k);
+    if (rc != PTRT_OK) return rc;
+    const HostInst &h = b->inst[k];
+    const Geom g = inst_geom(h);
+    StageRing ring(b->pool, h.N, 9 * sizeof(double), b->stream);
+    const hipError_t e = ring.out(
+        [&](char *buffer, long long n0, long long count) {
+            NodeRange r{};
+            r.n0 = (unsigned)n0;
+            r.count = (unsigned)count;
+            dispatch_storage(b->storage, h.has_mask, [&](auto st, auto mk) -> int {
+                using S = typename decltype(st)::type;
+                hipLaunchKernelGGL((k_read_state<D2Q9, S, decltype(mk)::value, false, double>),
+                                   dim3((unsigned)((count + 255) / 256)), dim3(256), 0, b->stream,
+                                   (const S *)b->buf[b->cur] + h.off, b->d_mask + h.moff, g, r,
+                                   (double *)buffer);
+                return PTRT_OK;
+            });
+        },
+        [&](char *buffer, long long n0, long long count, long long a, long long z) {
+            for (int i = 0; i < 9; ++i)
+                std::memcpy(f + (size_t)i * h.N + n0 + a, (const double *)buffer + i * count + a,
+                            (size_t)(z - a) * sizeof(double));
+        });
+    if (e != hipSuccess) return bfail_hip(b, PTRT_EDEVICE, std::string("download: ") + hipGetErrorString(e));
+    return PTRT_OK;
 }
 
 int ptrt_batch_diagnostics(ptrt_batch *b, double *mass, double *ke)
@@ -1011,9 +1057,8 @@ int ptrt_batch_diagnostics(ptrt_batch *b, double *mass, double *ke)
             using S = typename decltype(st)::type;
             constexpr bool M = decltype(mk)::value;
             hipLaunchKernelGGL((k_gather<L, S, M>), grid, dim3(BLK_X, BLK_Y, 1), 0, b->stream,
-                               (const S *)b->buf[b->cur] + h.off, b->d_mask + h.moff, g, 0, h.force[0],
-                               h.force[1], 0.0, (double *)nullptr, (double *)nullptr, (double *)nullptr,
-                               0LL, b->d_partials);
+                               (const S *)b->buf[b->cur] + h.off, b->d_mask + h.moff, g, h.force[0],
+                               h.force[1], 0.0, b->d_partials);
             return PTRT_OK;
         });
         hipLaunchKernelGGL(k_finalize<1024>, dim3(1), dim3(1024), 0, b->stream, b->d_partials,

@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "host_common.hpp"
+#include "host_stage.hpp"
 #include "step_launch.hpp"
 #include "tile_launch.hpp"
 
@@ -62,6 +63,7 @@ struct ptrt_ctx {
     double2 *d_partials = nullptr;
     int nparts = 0;
     double *d_red = nullptr;
+    std::shared_ptr<HostPool> pool; // host threads and pinned memory of the transfers
     hipStream_t stream = nullptr;
     bool allocated = false, initialized = false;
     long long t = 0;
@@ -133,14 +135,6 @@ dim3 gather_grid(const ptrt_ctx *c, int nzs)
     return dim3((c->nx + BLK_X - 1) / BLK_X, (c->ny + BLK_Y - 1) / BLK_Y, nzs);
 }
 
-// z-slab height so that a [Q][slab] FP64 host transfer stays under ~512 MB
-int slab_planes(const ptrt_ctx *c, int per_node_doubles)
-{
-    const double plane = (double)c->nx * c->ny * per_node_doubles * 8.0;
-    int s = (int)std::max(1.0, 512.0 * 1024 * 1024 / plane);
-    return std::min(s, c->nz);
-}
-
 int ensure_phi(ptrt_ctx *c, int forcing);
 
 // Free what allocate_device has allocated (after a failure part way, so
@@ -167,6 +161,8 @@ int allocate_device(ptrt_ctx *c);
 int ensure_allocated(ptrt_ctx *c)
 {
     if (c->allocated) return PTRT_OK;
+    c->pool = HostPool::shared();
+    if (!c->pool) return fail(c, PTRT_ENOMEM, "out of host memory");
     const int rc = allocate_device(c);
     if (rc != PTRT_OK) {
         release_device(c);
@@ -321,126 +317,201 @@ int allocate_device(ptrt_ctx *c)
 
 Geom geom(const ptrt_ctx *c) { return c->geo; }
 
-// Scatter host data (equilibrium from rho/u, or populations f) into the
-// current buffer, slab by slab.
-int upload_state(ptrt_ctx *c, const double *rho, const double *u, const double *f)
+NodeRange node_range(long long n0, long long count)
 {
-    const bool pops = f != nullptr;
-    const int per_node = pops ? c->Q : 4;
-    const int slab = slab_planes(c, per_node);
-    const long long plane = (long long)c->nx * c->ny;
-    double *d_in = nullptr;
-    const size_t in_elems = (size_t)per_node * slab * plane;
-    HIPCHK(c, hipMalloc(&d_in, in_elems * sizeof(double)));
-    int rc = PTRT_OK;
-    for (int z0 = 0; z0 < c->nz && rc == PTRT_OK; z0 += slab) {
-        const int nzs = std::min(slab, c->nz - z0);
-        const long long cnt = nzs * plane;
-        const double *d_rho = nullptr, *d_u = nullptr;
-        hipError_t e = hipSuccess;
-        if (pops) {
-            for (int i = 0; i < c->Q && e == hipSuccess; ++i)
-                e = hipMemcpyAsync(d_in + (size_t)i * cnt, f + (size_t)i * c->N + z0 * plane,
-                                   cnt * sizeof(double), hipMemcpyHostToDevice, c->stream);
-        } else {
-            if (rho) {
-                e = hipMemcpyAsync(d_in, rho + z0 * plane, cnt * sizeof(double),
-                                   hipMemcpyHostToDevice, c->stream);
-                d_rho = d_in;
-            }
-            if (u && e == hipSuccess) {
-                const int D = c->lattice == PTRT_D2Q9 ? 2 : 3;
-                for (int a = 0; a < D && e == hipSuccess; ++a)
-                    e = hipMemcpyAsync(d_in + (size_t)(1 + a) * cnt, u + (size_t)a * c->N + z0 * plane,
-                                       cnt * sizeof(double), hipMemcpyHostToDevice, c->stream);
-                d_u = d_in + cnt;
-            }
-        }
-        if (e != hipSuccess) {
-            rc = fail_hip(c, PTRT_EDEVICE, std::string("host to device copy: ") + hipGetErrorString(e));
-            break;
-        }
-        const Geom g = geom(c);
-        void *dst = c->buf[c->cur];
-        const dim3 grid = gather_grid(c, nzs), block(BLK_X, BLK_Y, 1);
-        dispatch(c->lattice, c->storage, c->has_mask, [&](auto lt, auto st, auto mk) -> int {
-            using L = typename decltype(lt)::type;
-            using S = typename decltype(st)::type;
-            constexpr bool M = decltype(mk)::value;
-            with_open<L>(c, [&](auto oc) {
-                constexpr bool O = decltype(oc)::value;
-                if (pops)
-                    hipLaunchKernelGGL((k_set_state<L, S, M, O>), grid, block, 0, c->stream,
-                                       (S *)dst, c->d_mask, g, z0, d_in, cnt);
-                else
-                    hipLaunchKernelGGL((k_init_eq<L, S, M, O>), grid, block, 0, c->stream,
-                                       (S *)dst, c->d_mask, g, z0, d_rho, d_u, cnt);
-            });
-            return PTRT_OK;
-        });
-        e = hipGetLastError();
-        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-        if (e != hipSuccess) rc = fail_hip(c, PTRT_EDEVICE, std::string("state upload: ") + hipGetErrorString(e));
-    }
-    (void)hipFree(d_in);
-    return rc;
+    NodeRange r{};
+    r.n0 = (unsigned)n0;
+    r.count = (unsigned)count;
+    return r;
 }
 
-// Gather rho/u/f (any may be null) of the state at t to host arrays.
-int download_state(ptrt_ctx *c, double *rho, double *u, double *f)
+dim3 node_grid(long long count) { return dim3((unsigned)((count + 255) / 256)); }
+
+int components(const ptrt_ctx *c) { return c->lattice == PTRT_D2Q9 ? 2 : 3; }
+
+// Populations cross to the host as FP32 shifted values where these are
+// exact: the shift is added, and taken off, on the host with the same FP64
+// operation and rounding, and half the bytes go over PCIe.  Open boundaries
+// compute some populations in FP64.
+bool narrow_populations(const ptrt_ctx *c) { return storage_bytes(c->storage) <= 4 && !c->open; }
+
+// Scatter host data (equilibrium from rho/u) into the current buffer.
+int upload_fields(ptrt_ctx *c, const double *rho, const double *u)
 {
-    const int per_node = (f ? c->Q : 0) + (rho ? 1 : 0) + (u ? 3 : 0);
-    if (per_node == 0) return PTRT_OK;
-    const int slab = slab_planes(c, per_node);
-    const long long plane = (long long)c->nx * c->ny;
-    double *d_out = nullptr;
-    HIPCHK(c, hipMalloc(&d_out, (size_t)per_node * slab * plane * sizeof(double)));
-    int rc = PTRT_OK;
-    for (int z0 = 0; z0 < c->nz; z0 += slab) {
-        const int nzs = std::min(slab, c->nz - z0);
-        const long long cnt = nzs * plane;
-        double *d_rho = rho ? d_out : nullptr;
-        double *d_u = u ? d_out + (rho ? cnt : 0) : nullptr;
-        double *d_f = f ? d_out + ((rho ? 1 : 0) + (u ? 3 : 0)) * cnt : nullptr;
-        const Geom g = geom(c);
-        const void *src = c->buf[c->cur];
-        const dim3 grid = gather_grid(c, nzs), block(BLK_X, BLK_Y, 1);
+    const int D = components(c), fields = (rho ? 1 : 0) + (u ? D : 0);
+    const Geom g = geom(c);
+    void *dst = c->buf[c->cur];
+    auto launch = [&](char *buffer, long long n0, long long count) {
+        const double *d_rho = rho ? (const double *)buffer : nullptr;
+        const double *d_u = u ? (const double *)buffer + (rho ? count : 0) : nullptr;
         dispatch(c->lattice, c->storage, c->has_mask, [&](auto lt, auto st, auto mk) -> int {
             using L = typename decltype(lt)::type;
             using S = typename decltype(st)::type;
             constexpr bool M = decltype(mk)::value;
             with_open<L>(c, [&](auto oc) {
-                constexpr bool O = decltype(oc)::value;
-                hipLaunchKernelGGL((k_gather<L, S, M, O>), grid, block, 0, c->stream,
-                                   (const S *)src, c->d_mask, g, z0, c->g[0], c->g[1], c->g[2],
-                                   d_rho, d_u, d_f, cnt, (double2 *)nullptr);
+                hipLaunchKernelGGL((k_init_eq<L, S, M, decltype(oc)::value>), node_grid(count), dim3(256),
+                                   0, c->stream, (S *)dst, c->d_mask, g, node_range(n0, count), d_rho, d_u);
             });
             return PTRT_OK;
         });
-        hipError_t e = hipGetLastError();
-        if (e == hipSuccess && rho)
-            e = hipMemcpyAsync(rho + z0 * plane, d_rho, cnt * sizeof(double), hipMemcpyDeviceToHost, c->stream);
-        if (u) {
-            const int D = c->lattice == PTRT_D2Q9 ? 2 : 3;
-            for (int a = 0; a < 3 && e == hipSuccess; ++a) {
-                if (a < D)
-                    e = hipMemcpyAsync(u + (size_t)a * c->N + z0 * plane, d_u + (size_t)a * cnt,
-                                       cnt * sizeof(double), hipMemcpyDeviceToHost, c->stream);
-            }
-        }
-        if (f)
-            for (int i = 0; i < c->Q && e == hipSuccess; ++i)
-                e = hipMemcpyAsync(f + (size_t)i * c->N + z0 * plane, d_f + (size_t)i * cnt,
-                                   cnt * sizeof(double), hipMemcpyDeviceToHost, c->stream);
+    };
+    hipError_t e;
+    if (fields == 0) {
+        launch(nullptr, 0, c->N);
+        e = hipGetLastError();
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-        if (e != hipSuccess) {
-            rc = fail_hip(c, PTRT_EDEVICE, std::string("state download: ") + hipGetErrorString(e));
-            break;
-        }
+    } else {
+        StageRing ring(c->pool, c->N, fields * sizeof(double), c->stream);
+        e = ring.in(
+            [&](char *buffer, long long n0, long long count, long long a, long long b) {
+                double *to = (double *)buffer;
+                const size_t bytes = (size_t)(b - a) * sizeof(double);
+                if (rho) {
+                    std::memcpy(to + a, rho + n0 + a, bytes);
+                    to += count;
+                }
+                for (int k = 0; u && k < D; ++k)
+                    std::memcpy(to + k * count + a, u + (size_t)k * c->N + n0 + a, bytes);
+            },
+            launch);
     }
-    if (u && c->lattice == PTRT_D2Q9) std::memset(u + 2 * (size_t)c->N, 0, (size_t)c->N * sizeof(double));
-    (void)hipFree(d_out);
-    return rc;
+    if (e != hipSuccess) return fail_hip(c, PTRT_EDEVICE, std::string("state upload: ") + hipGetErrorString(e));
+    return PTRT_OK;
+}
+
+// f(V{}) for the type in which populations cross to the host; OPEN only
+// with double.
+template <class F>
+void with_population_type(const ptrt_ctx *c, F &&f)
+{
+    if (narrow_populations(c)) f(float{});
+    else f(double{});
+}
+
+// Scatter populations f[Q][N] into the current buffer.
+int upload_populations(ptrt_ctx *c, const double *f)
+{
+    const Geom g = geom(c);
+    void *dst = c->buf[c->cur];
+    double w[27];
+    ptrt_velocity_set(c->lattice, nullptr, w);
+    hipError_t e = hipSuccess;
+    with_population_type(c, [&](auto v) {
+        using V = decltype(v);
+        StageRing ring(c->pool, c->N, c->Q * sizeof(V), c->stream);
+        e = ring.in(
+            [&](char *buffer, long long n0, long long count, long long a, long long b) {
+                for (int i = 0; i < c->Q; ++i) {
+                    V *to = (V *)buffer + (size_t)i * count;
+                    const double *from = f + (size_t)i * c->N + n0;
+                    const double wi = sizeof(V) == 4 ? w[i] : 0.0;
+                    for (long long n = a; n < b; ++n) to[n] = (V)(from[n] - wi);
+                }
+            },
+            [&](char *buffer, long long n0, long long count) {
+                dispatch(c->lattice, c->storage, c->has_mask, [&](auto lt, auto st, auto mk) -> int {
+                    using L = typename decltype(lt)::type;
+                    using S = typename decltype(st)::type;
+                    constexpr bool M = decltype(mk)::value;
+                    with_open<L>(c, [&](auto oc) {
+                        constexpr bool O = decltype(oc)::value;
+                        if constexpr (sizeof(V) == 8 || (sizeof(S) <= 4 && !O))
+                            hipLaunchKernelGGL((k_set_state<L, S, M, O, V>), node_grid(count), dim3(256), 0,
+                                               c->stream, (S *)dst, c->d_mask, g, node_range(n0, count),
+                                               (const V *)buffer);
+                    });
+                    return PTRT_OK;
+                });
+            });
+    });
+    if (e != hipSuccess) return fail_hip(c, PTRT_EDEVICE, std::string("state upload: ") + hipGetErrorString(e));
+    return PTRT_OK;
+}
+
+// Density and velocity of the state at t to host arrays (either may be null).
+int download_moments(ptrt_ctx *c, double *rho, double *u)
+{
+    const int D = components(c), fields = (rho ? 1 : 0) + (u ? D : 0);
+    if (fields == 0) return PTRT_OK;
+    const Geom g = geom(c);
+    const void *src = c->buf[c->cur];
+    StageRing ring(c->pool, c->N, fields * sizeof(double), c->stream);
+    const hipError_t e = ring.out(
+        [&](char *buffer, long long n0, long long count) {
+            double *d_rho = rho ? (double *)buffer : nullptr;
+            double *d_u = u ? (double *)buffer + (rho ? count : 0) : nullptr;
+            dispatch(c->lattice, c->storage, c->has_mask, [&](auto lt, auto st, auto mk) -> int {
+                using L = typename decltype(lt)::type;
+                using S = typename decltype(st)::type;
+                constexpr bool M = decltype(mk)::value;
+                with_open<L>(c, [&](auto oc) {
+                    hipLaunchKernelGGL((k_read_moments<L, S, M, decltype(oc)::value>), node_grid(count),
+                                       dim3(256), 0, c->stream, (const S *)src, c->d_mask, g,
+                                       node_range(n0, count), c->g[0], c->g[1], c->g[2], d_rho, d_u);
+                });
+                return PTRT_OK;
+            });
+        },
+        [&](char *buffer, long long n0, long long count, long long a, long long b) {
+            const double *from = (const double *)buffer;
+            const size_t bytes = (size_t)(b - a) * sizeof(double);
+            if (rho) {
+                std::memcpy(rho + n0 + a, from + a, bytes);
+                from += count;
+            }
+            for (int k = 0; u && k < D; ++k)
+                std::memcpy(u + (size_t)k * c->N + n0 + a, from + k * count + a, bytes);
+            if (u && D == 2) std::memset(u + 2 * (size_t)c->N + n0 + a, 0, bytes);
+        });
+    if (e != hipSuccess) return fail_hip(c, PTRT_EDEVICE, std::string("state download: ") + hipGetErrorString(e));
+    return PTRT_OK;
+}
+
+// Populations f[Q][N] of the state at t to a host array.
+int download_populations(ptrt_ctx *c, double *f)
+{
+    const Geom g = geom(c);
+    const void *src = c->buf[c->cur];
+    double w[27];
+    ptrt_velocity_set(c->lattice, nullptr, w);
+    hipError_t e = hipSuccess;
+    with_population_type(c, [&](auto v) {
+        using V = decltype(v);
+        StageRing ring(c->pool, c->N, c->Q * sizeof(V), c->stream);
+        e = ring.out(
+            [&](char *buffer, long long n0, long long count) {
+                dispatch(c->lattice, c->storage, c->has_mask, [&](auto lt, auto st, auto mk) -> int {
+                    using L = typename decltype(lt)::type;
+                    using S = typename decltype(st)::type;
+                    constexpr bool M = decltype(mk)::value;
+                    with_open<L>(c, [&](auto oc) {
+                        constexpr bool O = decltype(oc)::value;
+                        if constexpr (sizeof(V) == 8 || (sizeof(S) <= 4 && !O))
+                            hipLaunchKernelGGL((k_read_state<L, S, M, O, V>), node_grid(count), dim3(256),
+                                               0, c->stream, (const S *)src, c->d_mask, g,
+                                               node_range(n0, count), (V *)buffer);
+                    });
+                    return PTRT_OK;
+                });
+            },
+            [&](char *buffer, long long n0, long long count, long long a, long long b) {
+                for (int i = 0; i < c->Q; ++i) {
+                    const V *from = (const V *)buffer + (size_t)i * count;
+                    double *to = f + (size_t)i * c->N + n0;
+                    if (sizeof(V) == 8) {
+                        std::memcpy(to + a, from + a, (size_t)(b - a) * sizeof(V));
+                        continue;
+                    }
+                    const double wi = w[i];
+                    for (long long n = a; n < b; ++n) to[n] = (double)from[n] + wi;
+                    if (c->has_mask)
+                        for (long long n = a; n < b; ++n)
+                            if (c->h_mask[(size_t)(n0 + n)]) to[n] = 0.0;
+                }
+            });
+    });
+    if (e != hipSuccess) return fail_hip(c, PTRT_EDEVICE, std::string("state download: ") + hipGetErrorString(e));
+    return PTRT_OK;
 }
 
 StepLaunch step_args(const ptrt_ctx *c, hipStream_t s);
@@ -880,7 +951,7 @@ int ptrt_init_equilibrium(ptrt_ctx *c, const double *rho, const double *u)
     if (!c) return PTRT_EINVAL;
     int rc = ensure_allocated(c);
     if (rc != PTRT_OK) return rc;
-    rc = upload_state(c, rho, u, nullptr);
+    rc = upload_fields(c, rho, u);
     if (rc != PTRT_OK) return rc;
     c->initialized = true;
     c->t = 0;
@@ -892,7 +963,7 @@ int ptrt_set_populations(ptrt_ctx *c, const double *f)
     if (!c || !f) return fail(c, PTRT_EINVAL, "NULL argument");
     int rc = ensure_allocated(c);
     if (rc != PTRT_OK) return rc;
-    rc = upload_state(c, nullptr, nullptr, f);
+    rc = upload_populations(c, f);
     if (rc != PTRT_OK) return rc;
     c->initialized = true;
     return reset_check(c);
@@ -934,14 +1005,14 @@ int ptrt_moments(ptrt_ctx *c, double *rho_out, double *u_out)
 {
     if (!c) return PTRT_EINVAL;
     if (!c->initialized) return fail(c, PTRT_ESTATE, "moments before init");
-    return download_state(c, rho_out, u_out, nullptr);
+    return download_moments(c, rho_out, u_out);
 }
 
 int ptrt_get_populations(ptrt_ctx *c, double *f_out)
 {
     if (!c || !f_out) return fail(c, PTRT_EINVAL, "NULL argument");
     if (!c->initialized) return fail(c, PTRT_ESTATE, "get_populations before init");
-    return download_state(c, nullptr, nullptr, f_out);
+    return download_populations(c, f_out);
 }
 
 int ptrt_diagnostics(ptrt_ctx *c, double *mass, double *ke)
@@ -958,8 +1029,7 @@ int ptrt_diagnostics(ptrt_ctx *c, double *mass, double *ke)
         with_open<L>(c, [&](auto oc) {
             constexpr bool O = decltype(oc)::value;
             hipLaunchKernelGGL((k_gather<L, S, M, O>), grid, block, 0, c->stream, (const S *)src,
-                               c->d_mask, g, 0, c->g[0], c->g[1], c->g[2], (double *)nullptr,
-                               (double *)nullptr, (double *)nullptr, 0LL, c->d_partials);
+                               c->d_mask, g, c->g[0], c->g[1], c->g[2], c->d_partials);
         });
         return PTRT_OK;
     });
