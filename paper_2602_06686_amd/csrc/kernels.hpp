@@ -572,11 +572,10 @@ k_gather(const S *__restrict__ src, const uint8_t *__restrict__ mask, Geom g, do
     if (threadIdx.x == 0 && threadIdx.y == 0) partials[flat_block()] = make_double2(m, k);
 }
 
-// Sum nparts partials in a fixed order (deterministic) into out[0..1].
-// (A template only so that every translation unit may instantiate it.)
-template <int BLOCK = 1024>
-__global__ void __launch_bounds__(BLOCK)
-k_finalize(const double2 *__restrict__ partials, int nparts, double *__restrict__ out)
+// Sum nparts partials in a fixed order (deterministic) into out[0..1], by
+// one workgroup.
+__device__ __forceinline__ void sum_partials(const double2 *__restrict__ partials, int nparts,
+                                             double *__restrict__ out)
 {
     double a = 0.0, b = 0.0;
     for (int i = threadIdx.x; i < nparts; i += blockDim.x) {
@@ -588,6 +587,14 @@ k_finalize(const double2 *__restrict__ partials, int nparts, double *__restrict_
         out[0] = a;
         out[1] = b;
     }
+}
+
+// (A template only so that every translation unit may instantiate it.)
+template <int BLOCK = 1024>
+__global__ void __launch_bounds__(BLOCK)
+k_finalize(const double2 *__restrict__ partials, int nparts, double *__restrict__ out)
+{
+    sum_partials(partials, nparts, out);
 }
 
 // Sum (a, b, c) over a workgroup of up to 1024 threads; valid in thread 0.

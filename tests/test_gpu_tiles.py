@@ -120,3 +120,31 @@ def test_batch(sizes, storage):
     for k, s in enumerate(specs):
         fluid = np.broadcast_to(True if s["mask"] is None else s["mask"] == 0, got[0][k].shape)
         assert np.array_equal(got[0][k][fluid], got[1][k][fluid]), f"instance {k}"
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16"])
+@pytest.mark.parametrize("count", [1, 2, 9])
+def test_batch_diagnostics_equal_single(count, storage):
+    """Mass and energy of all lattices from one launch: bit for bit those of
+    each lattice alone (same blocks, same order of sums)."""
+    print_case("batch diagnostics against single lattices", count, storage)
+    kinds = ["walls", "none", "random", "block"]
+    sizes = [(70, 9), (1, 1), (64, 4), (65, 5), (3, 200), (200, 3), (130, 61), (300, 333), (16, 16)][:count]
+    specs = [{"nx": nx, "ny": ny, "tau_plus": 0.7, "Lambda": 0.2, "g": (1e-5, -2e-6 * k, 0.0),
+              "mask": _mask(kinds[k % 4], ny, nx)} for k, (nx, ny) in enumerate(sizes)]
+    b = P.ptrt_batch_create(specs, storage)
+    try:
+        fields = [I.random_fields(np.random.default_rng(k), (1, ny, nx), umax=0.04)
+                  for k, (nx, ny) in enumerate(sizes)]
+        for k, (rho, u) in enumerate(fields):
+            P.ptrt_batch_init_equilibrium(b, k, rho, u[:2])
+        P.ptrt_batch_step(b, 5)
+        mass, energy = P.ptrt_batch_diagnostics(b)
+    finally:
+        P.ptrt_batch_destroy(b)
+    for k, s in enumerate(specs):
+        with P.Lattice(P.PTRT_D2Q9, s["nx"], s["ny"], 1, 0.7, 0.2, force=s["g"], solid_mask=s["mask"],
+                       storage=storage) as G:
+            G.init_equilibrium(fields[k][0], fields[k][1][:2])
+            G.step(5)
+            assert G.diagnostics() == (mass[k], energy[k])
