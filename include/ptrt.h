@@ -189,7 +189,8 @@ int ptrt_set_forcing(ptrt_ctx *ctx, int forcing);
  * (temporal blocking) where the configuration allows it and it measured
  * faster: PTRT_FORCING_SCHEME2 with PTRT_MODEL_PTRT (or, without solid
  * nodes or open x, PTRT_MODEL_TRT_RLB or PTRT_MODEL_TRT), and either D3Q19 in
- * FP32 or FP64 with nx a multiple of 64 and ny >= 4 (with solid nodes:
+ * FP32 or FP64 with nx a multiple of 64 and ny >= 4, or (PTRT_MODEL_PTRT
+ * without solid nodes) any nx from 24 on and 80 000 nodes on (with solid nodes:
  * from 2^24 nodes on, while at most 5 % of the kernel's column chunks have
  * a solid within one row), or D2Q9 in FP32 or FP64 (with solid nodes or
  * open x: from 2^20 nodes on, while at most 30 % of the rows lie in row

@@ -158,6 +158,9 @@ inline long long make_layout(int Q, int nx, int ny, int nz, size_t elem, Geom &g
     const int pitch = (int)(((long long)nx + line - 1) / line * line);
     int lr = 0;
     while (((long long)pitch << (lr + 1)) * (long long)elem <= 8192) ++lr;
+    // 3D: a plane is a whole number of tiles, so that a node's offset splits
+    // into a z part and an (x, y) part
+    while (Q > 9 && ny % (1 << lr) != 0) --lr;
     g.nx = nx;
     g.ny = ny;
     g.nz = nz;

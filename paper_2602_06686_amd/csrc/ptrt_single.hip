@@ -135,6 +135,16 @@ dim3 gather_grid(const ptrt_ctx *c, int nzs)
     return dim3((c->nx + BLK_X - 1) / BLK_X, (c->ny + BLK_Y - 1) / BLK_Y, nzs);
 }
 
+NodeRange node_range(long long n0, long long count)
+{
+    NodeRange r{};
+    r.n0 = (unsigned)n0;
+    r.count = (unsigned)count;
+    return r;
+}
+
+dim3 node_grid(long long count) { return dim3((unsigned)((count + 255) / 256)); }
+
 int ensure_phi(ptrt_ctx *c, int forcing);
 
 // Free what allocate_device has allocated (after a failure part way, so
@@ -316,16 +326,6 @@ int allocate_device(ptrt_ctx *c)
 }
 
 Geom geom(const ptrt_ctx *c) { return c->geo; }
-
-NodeRange node_range(long long n0, long long count)
-{
-    NodeRange r{};
-    r.n0 = (unsigned)n0;
-    r.count = (unsigned)count;
-    return r;
-}
-
-dim3 node_grid(long long count) { return dim3((unsigned)((count + 255) / 256)); }
 
 int components(const ptrt_ctx *c) { return c->lattice == PTRT_D2Q9 ? 2 : 3; }
 

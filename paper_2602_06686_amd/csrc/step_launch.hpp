@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "host_common.hpp"
+#include "march3d.hpp"
 #include "step2.hpp"
 
 namespace ptrt {
@@ -181,6 +182,90 @@ bool step2_3d_task_lists(const Geom &g, const uint8_t *near, std::vector<int4> &
     }
 }
 
+// Whether a pair of steps without solids runs the march of march3d.hpp.
+// Measured, us a step, before -> march: where k_step2 (nx a multiple of 64)
+// ran before, the march is faster below 800 000 nodes, whose few columns
+// leave k_step2's longer chains exposed (64^3 FP32 13.7 -> 8.2, FP64
+// 20.0 -> 13.8; 192 x 64 x 64 16.4 -> 14.5; 64 x 128 x 128 17.0 -> 22.2).
+// Where one step per pass ran, it is faster from 80 000 nodes on (40^3 4.8
+// -> 5.5, 48^3 5.8 -> 5.5, 100 x 84 x 92 FP32 22.4 -> 16.2, FP64 42.5 -> 30,
+// 300^3 FP32 970 -> 626, FP64 1584 -> 970) unless its rows are mostly idle
+// lanes: at least 24 columns, and in FP32 at least 42 once the lattice is
+// too large for the last-level cache to hide the others' loads (130^3, 44
+// columns, 67.4 -> 65.5).
+inline bool march_applies(const StepLaunch &a)
+{
+    const Geom &g = a.g;
+    if ((a.storage != PTRT_F32 && a.storage != PTRT_F64) || a.model != MODEL_PTRT || a.has_mask) return false;
+    const size_t elem = storage_bytes(a.storage);
+    // 32-bit offsets inside a plane of whole layout tiles
+    if (g.ny % (1 << g.lr) != 0 || (double)(g.ny >> g.lr) * (double)g.tile * (double)elem >= 4294967296.0)
+        return false;
+    const double nodes = (double)g.nx * g.ny * g.nz;
+    if (g.nx % Step2Shape<D3Q19, float>::BX == 0 && g.ny >= Step2Shape<D3Q19, float>::BY) return nodes < 8e5;
+    const int cols = march_cols(g.nx);
+    return nodes >= 8e4 && cols >= (elem == 4 && nodes > 1.5e6 ? 42 : 24);
+}
+
+// Planes per chunk: as step2_3d_zc, down to single planes (a small lattice
+// takes short chains over many workgroups).
+template <class S, class SH>
+int march_zc(const Geom &g)
+{
+    static const int resident = [] {
+        int per_cu = 0, dev = 0, cus = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                &per_cu, reinterpret_cast<const void *>(&k_march3d<S, SH>), 64 * SH::AY, 0) != hipSuccess ||
+            hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+            per_cu <= 0 || cus <= 0)
+            return 256;
+        return per_cu * cus;
+    }();
+    const int cols = march_cols(g.nx);
+    const long long columns = (long long)((g.nx + cols - 1) / cols) * ((g.ny + SH::BY - 1) / SH::BY);
+    int zc = g.nz;
+    double best = -1.0;
+    for (int c = 1; c <= g.nz; ++c) {
+        const int z = (g.nz + c - 1) / c;
+        const long long wgs = columns * ((g.nz + z - 1) / z);
+        const double cost = (double)((wgs + resident - 1) / resident) * (z + 2);
+        if (best < 0 || cost < best) {
+            best = cost;
+            zc = z;
+        }
+        if (wgs >= 16LL * resident) break;
+    }
+    return zc;
+}
+
+template <class S>
+void launch_march(const StepLaunch &a, double *pass_bytes)
+{
+    using C = typename Codec<S>::compute;
+    const Coef<D3Q19, C> r = make_coef<D3Q19, C>(a.tau_plus, a.Lambda, a.force);
+    const double nodes = (double)a.g.nx * a.g.ny * a.g.nz;
+    if (pass_bytes) *pass_bytes = 2.0 * nodes * D3Q19::Q * sizeof(S);
+    auto go = [&](auto sh) {
+        using SH = decltype(sh);
+        const int cols = march_cols(a.g.nx), zc = march_zc<S, SH>(a.g);
+        const dim3 grid((a.g.nx + cols - 1) / cols, (a.g.ny + SH::BY - 1) / SH::BY, (a.g.nz + zc - 1) / zc);
+        hipLaunchKernelGGL((k_march3d<S, SH>), grid, dim3(64 * SH::AY), 0, a.stream, (const S *)a.src,
+                           (S *)a.dst, a.g, r, zc, cols);
+    };
+    // six rows share their halo better; on large FP32 lattices more rows in
+    // flight evict halo lines before the neighbouring columns read them
+    // (us a step, six / four rows: 100 x 84 x 92 16.2 / 19.8, 186^3 152 /
+    // 148, 300^3 729 / 626; FP64 300^3 971 / 975)
+    if constexpr (sizeof(S) == 4) {
+        if (nodes > 6e6) {
+            go(MarchShape<S, 4>{});
+            return;
+        }
+    }
+    go(MarchShape<S, 6>{});
+}
+
 template <class L>
 bool launch_step2_lattice(const StepLaunch &a, double *pass_bytes)
 {
@@ -264,6 +349,13 @@ bool launch_step2_lattice(const StepLaunch &a, double *pass_bytes)
         });
         return true;
     } else {
+        if constexpr (L::Q == 19) {
+            if (march_applies(a)) {
+                if (a.storage == PTRT_F64) launch_march<double>(a, pass_bytes);
+                else launch_march<float>(a, pass_bytes);
+                return true;
+            }
+        }
         if (a.has_mask && (!a.tasks_plain || !a.tasks_special)) return false;
         bool launched = false;
         dispatch_storage(a.storage, false, [&](auto st, auto) -> int {

@@ -148,3 +148,26 @@ def test_batch_diagnostics_equal_single(count, storage):
             G.init_equilibrium(fields[k][0], fields[k][1][:2])
             G.step(5)
             assert G.diagnostics() == (mass[k], energy[k])
+
+
+# D3Q19 march: one strip, two and four, with widths down to 24 columns; rows
+# and chunks that end ragged; one plane; widths that are multiples of 64 below
+# and above the other pass's range; four-row workgroups (FP32, large)
+@pytest.mark.parametrize("storage", ["f32", "f64"])
+@pytest.mark.parametrize("shape", [(60, 61, 24), (47, 45, 48), (1, 1500, 62), (90, 85, 101), (41, 2, 1000),
+                                   (92, 84, 100), (33, 70, 130), (30, 64, 64), (50, 100, 192),
+                                   (182, 183, 186)])
+def test_d3q19_march(shape, storage):
+    print_case("D3Q19 march against single steps", shape, storage)
+    nz, ny, nx = shape
+    rho, u = I.random_fields(np.random.default_rng(nx), shape, umax=0.04)
+    got = []
+    for spp in (1, 2):
+        with P.Lattice(P.PTRT_D3Q19, nx, ny, nz, 0.64, 0.2, force=[3e-6, -1e-6, 2e-6], storage=storage,
+                       steps_per_pass=spp) as G:
+            G.init_equilibrium(rho, u)
+            G.step(5)
+            G.step(2)
+            assert G.last_pass()[0] == spp
+            got.append(G.populations())
+    assert np.array_equal(got[0], got[1])
