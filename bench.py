@@ -156,7 +156,7 @@ def pass_accounting(res, nodes):
 
 
 def longer_passes(res, steps):
-    """D2Q9 calls of eight steps or more run in passes of up to ten steps and
+    """D2Q9 calls of eight steps or more run in passes of up to eight steps and
     end with one of two: the bytes of that last pass say nothing about the
     traffic of the others, so no bandwidth is derived from them."""
     if steps >= 8:

@@ -198,7 +198,7 @@ int ptrt_set_forcing(ptrt_ctx *ctx, int forcing);
  * step, runs one step per pass.  With 2, a call of ptrt_step with eight
  * steps or more on D2Q9 (any storage, PTRT_MODEL_PTRT or _PTRT_EXACT,
  * PTRT_FORCING_SCHEME2, or PTRT_FORCING_GUO with periodic x) runs all but
- * its last one or two steps in passes of up to ten on tiles kept in LDS,
+ * its last one or two steps in passes of up to eight on tiles kept in LDS,
  * where those are the faster ones, and ends with a pass of two steps or a
  * single step.  Results are bit-identical either way.
  * Allowed at any time (waits for the handle's stream). */
@@ -397,7 +397,7 @@ int ptrt_batch_autotune(ptrt_batch *b, int *tile_x, int *tile_y, int *blocks, in
 
 /* Enqueue n steps over every instance.  With eight steps or more and two
  * steps per pass (below), all but the last one or two run in passes of up to
- * ten steps on tiles kept in LDS where those are the faster ones, as
+ * eight steps on tiles kept in LDS where those are the faster ones, as
  * ptrt_set_steps_per_pass describes for a single lattice, and the call ends
  * with a pass of two steps or a single step.  Otherwise HIP graphs of ten
  * steps are replayed: pairs of steps as two-step passes, else one launch

@@ -519,7 +519,7 @@ void launch_tile_pass(ptrt_batch *b, int T)
     b->last_steps = T;
     dispatch_storage(b->storage, false, [&](auto st, auto) -> int {
         launch_tile_batch<typename decltype(st)::type>(b->buf[b->cur], b->buf[b->cur ^ 1], b->d_mask,
-                                                       b->d_inst, b->d_tile_tasks, b->n_tile_tasks,
+                                                       b->d_near, b->d_inst, b->d_tile_tasks, b->n_tile_tasks,
                                                        b->tile.shape, T, b->stream);
         return PTRT_OK;
     });

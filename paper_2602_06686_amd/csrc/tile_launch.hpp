@@ -48,13 +48,12 @@ inline int tile_core(int n, int most)
 //
 // A tile pass costs a launch (c0) and rounds of the workgroups a CU holds:
 // a round takes its issue time (rows of 64 nodes over all steps, q each,
-// plus the exposed part mem of the first step's loads), or the dependent
-// chain of one workgroup (lat per iteration of its waves, plus beta of its
+// and mem for the first step's loads), or the dependent chain of one workgroup (lat per iteration of its waves, plus beta of its
 // own issue time) if that is longer; the bytes it moves add their time at
-// bw.  Fitted to 210 (FP32) and 180 (FP64) timings of 64^2 ... 2048^2 with
-// T = 3 ... 10 (7 % and 5 % root mean square): the rule picks the fastest
-// pass timed at every size in FP32, and in FP64 one within 4 % of it.  The
-// earlier passes take about 2 us a launch and run at 113 (FP32), 64 (FP64)
+// bw.  The constants are those that choose best among the shapes with T =
+// 3 ... 8 timed on fourteen lattices and batches (64^2 ... 4096^2, FP32 and
+// FP64): the fastest pass at twelve, within 6 % (700^2) and 2 % of it at the
+// others.  The earlier passes take about 2 us a launch and run at 113 (FP32), 64 (FP64)
 // and 180 (16 bits) nodes a ns over rows padded to whole strips; they stay
 // faster on lattices of one or two rows, where a tile is mostly halo
 // (600000 x 1 FP32 6.2 us a step against 18.5), and for stochastic rounding
@@ -64,8 +63,11 @@ inline TilePlan choose_tile_plan(int storage, const std::vector<std::pair<int, i
 {
     const size_t elem = storage_bytes(storage);
     const bool f64 = elem == 8, sr = storage == PTRT_F16_SR || storage == PTRT_BF16_SR;
-    const double c0 = 3.0, lat = 0.2, q = f64 ? 0.06 : (sr ? 0.08 : 0.04), mem = f64 ? 0.0 : 0.5,
-                 bw = f64 ? 10e6 : 15e6, beta = f64 ? 1.0 : 0.8; // us, bytes per us
+    const bool half = elem == 2;
+    const double c0 = f64 ? 3.5 : (half ? 3.0 : 2.5), lat = f64 ? 0.3 : (half ? 0.2 : 0.15),
+                 q = f64 ? 0.045 : (sr ? 0.08 : (half ? 0.04 : 0.03)),
+                 mem = half ? 0.5 : 0.0, bw = f64 ? 10e6 : (half ? 15e6 : 5e6),
+                 beta = f64 || half ? 0.8 : 0.4; // us, bytes per us
     const double earlier_rate = f64 ? 64e3 : (elem == 4 ? 113e3 : 180e3); // nodes per us
     const int strip = elem == 2 ? 64 : Step2Shape2D<float>::BX;
     const int waves_per_cu = f64 || sr ? 16 : 32;
@@ -83,7 +85,7 @@ inline TilePlan choose_tile_plan(int storage, const std::vector<std::pair<int, i
             const int lds = (int)(SH::elems * elem) + 2 * SH::W * SH::H;
             const int occ = std::min(163840 / lds, waves_per_cu / SH::NW);
             if (occ < 1) return;
-            for (int T = 3; T <= 10; ++T) {
+            for (int T = 3; T <= 8; ++T) {
                 const int mw = SH::W - 2 * (T - 1), mh = SH::H - 2 * (T - 1);
                 if (mw < 1 || mh < 1) break;
                 long long tiles = 0;
@@ -188,7 +190,7 @@ private:
 template <class S>
 void launch_tile(const StepLaunch &a, const TilePlan &plan, const uint8_t *special, int T);
 template <class S>
-void launch_tile_batch(const void *src, void *dst, const uint8_t *mask, const void *inst,
+void launch_tile_batch(const void *src, void *dst, const uint8_t *mask, const uint8_t *near, const void *inst,
                        const int4 *tasks, int ntasks, int shape, int T, hipStream_t stream);
 
 // Definitions, for the translation units that instantiate them.
@@ -202,7 +204,7 @@ void launch_tile_impl(const StepLaunch &a, const TilePlan &plan, const uint8_t *
         auto go = [&](auto fc, auto oc) {
             hipLaunchKernelGGL((k_tile_2d<S, SH, decltype(fc)::value, decltype(oc)::value>),
                                dim3(plan.tiles), dim3(64 * SH::NW), 0, a.stream, (const S *)a.src,
-                               (S *)a.dst, a.mask, special, a.g, r, T, plan.cw, plan.ch, plan.tiles_x);
+                               (S *)a.dst, a.mask, a.near, special, a.g, r, T, plan.cw, plan.ch, plan.tiles_x);
         };
         using II = std::integral_constant<int, FORCE_II>;
         using GUO = std::integral_constant<int, FORCE_GUO>;
@@ -213,14 +215,14 @@ void launch_tile_impl(const StepLaunch &a, const TilePlan &plan, const uint8_t *
 }
 
 template <class S>
-void launch_tile_batch_impl(const void *src, void *dst, const uint8_t *mask, const void *inst,
+void launch_tile_batch_impl(const void *src, void *dst, const uint8_t *mask, const uint8_t *near, const void *inst,
                             const int4 *tasks, int ntasks, int shape, int T, hipStream_t stream)
 {
     using C = typename Codec<S>::compute;
     with_tile_shape(shape, [&](auto sh) {
         using SH = decltype(sh);
         hipLaunchKernelGGL((k_batch_tile<S, SH>), dim3(ntasks), dim3(64 * SH::NW), 0, stream,
-                           (const S *)src, (S *)dst, mask, (const BInst<C> *)inst, tasks, T);
+                           (const S *)src, (S *)dst, mask, near, (const BInst<C> *)inst, tasks, T);
     });
 }
 
@@ -231,10 +233,10 @@ void launch_tile_batch_impl(const void *src, void *dst, const uint8_t *mask, con
         launch_tile_impl<S>(a, plan, special, T);                                                    \
     }                                                                                                \
     template <>                                                                                      \
-    void launch_tile_batch<S>(const void *src, void *dst, const uint8_t *mask, const void *inst,     \
+    void launch_tile_batch<S>(const void *src, void *dst, const uint8_t *mask, const uint8_t *near, const void *inst,     \
                               const int4 *tasks, int ntasks, int shape, int T, hipStream_t stream)   \
     {                                                                                                \
-        launch_tile_batch_impl<S>(src, dst, mask, inst, tasks, ntasks, shape, T, stream);            \
+        launch_tile_batch_impl<S>(src, dst, mask, near, inst, tasks, ntasks, shape, T, stream);            \
     }
 
 } // namespace ptrt
