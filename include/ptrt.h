@@ -184,24 +184,26 @@ int ptrt_set_model(ptrt_ctx *ctx, int model);
  * fails.  Default PTRT_FORCING_SCHEME2. */
 int ptrt_set_forcing(ptrt_ctx *ctx, int forcing);
 
-/* Steps per pass over the populations (1 or 2; default 2).  With 2, pairs
- * of steps run as one kernel that keeps the first step's results in LDS
- * (temporal blocking) where the configuration allows it and it measured
- * faster: PTRT_FORCING_SCHEME2 with PTRT_MODEL_PTRT (or, without solid
- * nodes or open x, PTRT_MODEL_TRT_RLB or PTRT_MODEL_TRT), and either D3Q19 in
- * FP32 or FP64 with nx a multiple of 64 and ny >= 4, or (PTRT_MODEL_PTRT
- * without solid nodes) any nx from 24 on and 80 000 nodes on (with solid nodes:
- * from 2^24 nodes on, while at most 5 % of the kernel's column chunks have
- * a solid within one row), or D2Q9 in FP32 or FP64 (with solid nodes or
- * open x: from 2^20 nodes on, while at most 30 % of the rows lie in row
- * chunks with a solid within one row); every other case, and an odd last
- * step, runs one step per pass.  With 2, a call of ptrt_step with eight
- * steps or more on D2Q9 (any storage, PTRT_MODEL_PTRT or _PTRT_EXACT,
- * PTRT_FORCING_SCHEME2, or PTRT_FORCING_GUO with periodic x) runs all but
- * its last one or two steps in passes of up to eight on tiles kept in LDS,
- * where those are the faster ones, and ends with a pass of two steps or a
- * single step.  Results are bit-identical either way.
- * Allowed at any time (waits for the handle's stream). */
+/* Steps per pass over the populations (1 or 2; default 2).  With 2, several
+ * steps run as one kernel that keeps what lies between them in LDS (temporal
+ * blocking) where the configuration allows it and it measured faster:
+ * PTRT_FORCING_SCHEME2 with PTRT_MODEL_PTRT (or, without solid nodes or open
+ * x, PTRT_MODEL_TRT_RLB or PTRT_MODEL_TRT), and
+ * - D3Q19 in FP32 or FP64, pairs of steps: nx a multiple of 64 and ny >= 4
+ *   (with solid nodes: from 2^24 nodes on, while at most 5 % of the kernel's
+ *   column chunks have a solid within one row); with PTRT_MODEL_PTRT also
+ *   other nx from 24 on, from 80 000 nodes on, and there with solid nodes
+ *   (any nx; in FP32 up to 6 million nodes) in calls of eight steps or more;
+ * - D2Q9 in FP32 or FP64, pairs of steps: any size (with solid nodes or open
+ *   x: from 2^20 nodes on, while at most 30 % of the rows lie in row chunks
+ *   with a solid within one row);
+ * - D2Q9 in calls of eight steps or more (any storage type, solid nodes and
+ *   open x, PTRT_MODEL_PTRT or _PTRT_EXACT; also PTRT_FORCING_GUO with
+ *   periodic x): all but the last one or two steps in passes of up to eight,
+ *   then a pass of two steps or a single step.
+ * Every other case, and an odd last step, runs one step per pass.  Results
+ * are bit-identical either way.  Allowed at any time (waits for the handle's
+ * stream). */
 int ptrt_set_steps_per_pass(ptrt_ctx *ctx, int steps);
 
 /* The most recent kernel pass enqueued by ptrt_step: *steps = the steps it

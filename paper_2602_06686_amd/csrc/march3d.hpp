@@ -1,6 +1,6 @@
-// Two fused steps per pass for D3Q19 without solids on lattices of any
-// width, and on small ones (the counterpart of k_step2, which needs nx a
-// multiple of 64 and many columns).
+// Two fused steps per pass for D3Q19 on lattices of any width, on small
+// ones, and with solids (the counterpart of k_step2, which needs nx a
+// multiple of 64, many columns and no solid near them).
 //
 // A workgroup owns a column of cols (at most 62) x BY nodes and marches up a
 // chunk of planes like k_step2, but a wave's row holds the halo columns too
@@ -13,6 +13,13 @@
 // planes, about 4 us each with two workgroups on a CU.  The strips start
 // anywhere in a 128-byte line: plain stores, whose parts meet in L2 (the
 // non-temporal ones of k_step2 measured up to 13 % slower here).
+//
+// SOLID: link flags per node, formed once per lattice, are loaded one plane
+// before the pulls that depend on them; a row of 64 nodes without any takes
+// the plain code, so walls and blocks cost the rows at them only.  What
+// bounces back in the second step is the node's own first-step value, in LDS
+// for e_z >= 0 and, for the e_z = -1 class that LDS keeps for one plane, in
+// the wave's registers.
 #pragma once
 
 #include "step2.hpp"
@@ -26,18 +33,41 @@ inline int march_cols(int nx)
     return (nx + strips - 1) / strips;
 }
 
+// Link flags of every node, once per lattice: bit i: the source of
+// population i is solid, bit 0: the node is.
+template <class L>
+__global__ void __launch_bounds__(256)
+k_link_flags(const uint8_t *__restrict__ mask, Geom g, NodeRange r, unsigned *__restrict__ flags)
+{
+    if (!r.place(g)) return;
+    const Nbr n(g, r.x, r.y, r.z);
+    unsigned f = mask[r.node] ? 1u : 0u;
+    static_for<L::Q>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        if constexpr (i != 0) {
+            int sx;
+            unsigned srow;
+            source_of<L, i>(g, n, r.x, r.y, r.z, sx, srow);
+            if (mask[srow * (unsigned)g.nx + (unsigned)sx]) f |= 1u << i;
+        }
+    });
+    flags[r.node] = f;
+}
+
 template <class S, int BY_>
 struct MarchShape {
     static constexpr int W = 64, BY = BY_, AY = BY + 2, AP = AY * W;
     using K = Step2Classes<D3Q19, 2>;
     static constexpr int PAD = W; // sources of the garbage lanes 0 and 63
     static constexpr int elems = K::planes * AP + 2 * PAD;
+    template <class T>
+    static constexpr int waves_per_simd = sizeof(T) == 8 ? 2 : (BY == 6 ? 4 : 3);
 };
 
-template <class S, class SH>
+template <class S, class SH, bool SOLID>
 __global__ void __launch_bounds__((64 * SH::AY))
-__attribute__((amdgpu_waves_per_eu(sizeof(S) == 4 ? 4 : 2, sizeof(S) == 4 ? 4 : 2)))
-k_march3d(const S *__restrict__ src, S *__restrict__ dst, Geom g,
+__attribute__((amdgpu_waves_per_eu(SH::template waves_per_simd<S>, SH::template waves_per_simd<S>)))
+k_march3d(const S *__restrict__ src, S *__restrict__ dst, const unsigned *__restrict__ flags, Geom g,
           Coef<D3Q19, typename Codec<S>::compute> r, int zc, int cols)
 {
     using L = D3Q19;
@@ -73,22 +103,39 @@ k_march3d(const S *__restrict__ src, S *__restrict__ dst, Geom g,
                  (unsigned)sizeof(S);
     });
     const unsigned dir = (unsigned)g.plane * (unsigned)sizeof(S);
-    auto load = [&](int k, S (&raw)[L::Q]) __attribute__((always_inline)) {
+    // pull plane k; f: its link flags
+    auto load = [&](int k, unsigned f, S (&raw)[L::Q]) __attribute__((always_inline)) {
         const int gz = wrapz(k);
         const int zm = gz == 0 ? g.nz - 1 : gz - 1, zp = gz == g.nz - 1 ? 0 : gz + 1;
         const char *sb = reinterpret_cast<const char *>(src);
         const char *base[3] = {sb + (long long)zm * zstride, sb + (long long)gz * zstride,
                                sb + (long long)zp * zstride};
-        static_for<L::Q>([&](auto ic) {
-            constexpr int i = decltype(ic)::value;
-            raw[i] = *reinterpret_cast<const S *>(base[1 - L::ez(i)] + off[i]);
-        });
+        auto row = [&](auto bc) __attribute__((always_inline)) {
+            static_for<L::Q>([&](auto ic) {
+                constexpr int i = decltype(ic)::value;
+                const char *p = base[1 - L::ez(i)] + off[i];
+                if constexpr (decltype(bc)::value && i != 0)
+                    if ((f >> i) & 1u) p = base[1] + (off[0] + (unsigned)L::opp(i) * dir);
+                raw[i] = *reinterpret_cast<const S *>(p);
+            });
+        };
+        if (SOLID && __any(f != 0)) row(std::bool_constant<SOLID>{});
+        else row(std::false_type{});
+    };
+    const unsigned node = (unsigned)y * (unsigned)g.nx + (unsigned)x;
+    auto load_flags = [&](int k) -> unsigned {
+        if constexpr (SOLID) return flags[(size_t)wrapz(k) * ((size_t)g.ny * (size_t)g.nx) + node];
+        return 0u;
     };
     auto slot_of = [&](int i_cls, int i_idx, int slot, int a) {
         return (K::region(i_cls) + slot * K::count(i_cls) + i_idx) * AP + a;
     };
     const int own = w * W + lane;
-    auto first = [&](int it, const S (&raw)[L::Q]) __attribute__((always_inline)) {
+    // first step of plane `it`; down: with SOLID the e_z = -1 values, which
+    // LDS keeps for one plane only and a node above a solid takes back in its
+    // own second step, one iteration later
+    constexpr int ND = SOLID ? K::count(0) : 1;
+    auto first = [&](int it, const S (&raw)[L::Q], S (&down)[ND]) __attribute__((always_inline)) {
         C h[L::Q];
         static_for<L::Q>([&](auto ic) { h[decltype(ic)::value] = Codec<S>::load(&raw[decltype(ic)::value]); });
         C rho, ux, uy, uz;
@@ -96,47 +143,75 @@ k_march3d(const S *__restrict__ src, S *__restrict__ dst, Geom g,
         static_for<L::Q>([&](auto ic) {
             constexpr int i = decltype(ic)::value;
             constexpr int c = K::cls(i);
-            Codec<S>::template store<false>(&lds[slot_of(c, K::index(i), it % K::slots(c), own)], h[i]);
+            S v;
+            Codec<S>::template store<false>(&v, h[i]);
+            lds[slot_of(c, K::index(i), it % K::slots(c), own)] = v;
+            if constexpr (SOLID && c == 0) down[K::index(i)] = v;
         });
     };
-    // second step of plane k - 1, iteration it (first steps up to plane k)
-    auto second = [&](int k, int it) __attribute__((always_inline)) {
-        C h[L::Q];
-        static_for<L::Q>([&](auto ic) {
-            constexpr int i = decltype(ic)::value;
-            constexpr int c = K::cls(i);
-            h[i] = Codec<S>::load(
-                &lds[slot_of(c, K::index(i), (it - c) % K::slots(c), own - (L::ey(i) * W + L::ex(i)))]);
-        });
-        C rho, ux, uy, uz;
-        collide_pass<L, S>(h, r, rho, ux, uy, uz);
-        if (!b_lane) return;
-        char *db = reinterpret_cast<char *>(dst) + (long long)wrapz(k - 1) * zstride;
-        static_for<L::Q>([&](auto ic) {
-            constexpr int i = decltype(ic)::value;
-            Codec<S>::store(reinterpret_cast<S *>(db + (size_t)i * dir + off[0]), h[i]);
-        });
+    // second step of plane k - 1, iteration it (first steps up to plane k);
+    // f, down: flags and e_z = -1 values of plane k - 1
+    auto second = [&](int k, int it, unsigned f, const S (&down)[ND]) __attribute__((always_inline)) {
+        auto row = [&](auto bc) __attribute__((always_inline)) {
+            constexpr bool BACK = decltype(bc)::value;
+            C h[L::Q];
+            static_for<L::Q>([&](auto ic) {
+                constexpr int i = decltype(ic)::value;
+                constexpr int c = K::cls(i), o = L::opp(i), co = K::cls(o);
+                int a = slot_of(c, K::index(i), (it - c) % K::slots(c), own - (L::ey(i) * W + L::ex(i)));
+                if constexpr (BACK && i != 0 && co != 0)
+                    if ((f >> i) & 1u) a = slot_of(co, K::index(o), (it - 1) % K::slots(co), own);
+                h[i] = Codec<S>::load(&lds[a]);
+                if constexpr (BACK && i != 0 && co == 0)
+                    if ((f >> i) & 1u) h[i] = Codec<S>::load(&down[K::index(o)]);
+            });
+            C rho, ux, uy, uz;
+            collide_pass<L, S>(h, r, rho, ux, uy, uz);
+            if (!b_lane || (BACK && (f & 1u))) return;
+            char *db = reinterpret_cast<char *>(dst) + (long long)wrapz(k - 1) * zstride;
+            static_for<L::Q>([&](auto ic) {
+                constexpr int i = decltype(ic)::value;
+                Codec<S>::store(reinterpret_cast<S *>(db + (size_t)i * dir + off[0]), h[i]);
+            });
+        };
+        if (SOLID && __any(f != 0)) row(std::bool_constant<SOLID>{});
+        else row(std::false_type{});
     };
 
     // first steps of planes zs - 1, zs and zs + 1; then for k = zs + 1 ... ze
     // the second step of plane k - 1 and the first step of plane k + 1,
     // whose pulls were issued an iteration before (past the chunk the last
     // plane is loaded again)
-    S raw[L::Q];
-    load(zs - 1, raw);
-    first(0, raw);
-    load(zs, raw);
-    first(1, raw);
-    load(zs + 1, raw);
-    first(2, raw);
-    load(min(zs + 2, ze), raw);
+    S raw[L::Q], d0[ND], d1[ND], d2[ND]; // e_z = -1 values of planes k - 1, k, k + 1
+    unsigned f0 = load_flags(zs - 1), f1 = load_flags(zs), f2 = load_flags(zs + 1),
+             f3 = load_flags(min(zs + 2, ze));
+    load(zs - 1, f0, raw);
+    first(0, raw, d0);
+    load(zs, f1, raw);
+    first(1, raw, d0);
+    load(zs + 1, f2, raw);
+    first(2, raw, d1);
+    // f0 ... f3: flags of planes k - 1 ... k + 2
+    f0 = f1;
+    f1 = f2;
+    f2 = f3;
+    load(min(zs + 2, ze), f2, raw);
+    f3 = load_flags(min(zs + 3, ze));
     for (int k = zs + 1, it = 2;; ++k, ++it) {
         lds_barrier();
-        if (b_wave) second(k, it);
+        if (b_wave) second(k, it, f0, d0);
         lds_barrier();
         if (k == ze) break;
-        first(it + 1, raw);
-        load(min(k + 2, ze), raw);
+        first(it + 1, raw, d2);
+        for (int j = 0; j < ND; ++j) {
+            d0[j] = d1[j];
+            d1[j] = d2[j];
+        }
+        f0 = f1;
+        f1 = f2;
+        f2 = f3;
+        load(min(k + 2, ze), f2, raw);
+        f3 = load_flags(min(k + 3, ze));
     }
 }
 

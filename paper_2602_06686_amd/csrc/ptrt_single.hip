@@ -58,6 +58,7 @@ struct ptrt_ctx {
     // solid or an open x boundary in reach (null without either)
     TilePlan tile;
     uint8_t *d_special = nullptr;
+    unsigned *d_flags = nullptr; // D3Q19 with solids: link flags per node
     void *buf[2] = {nullptr, nullptr};
     int cur = 0;
     double2 *d_partials = nullptr;
@@ -157,7 +158,7 @@ void release_device(ptrt_ctx *c)
             p = nullptr;
         }
     void **owned[] = {(void **)&c->d_mask, (void **)&c->d_near, (void **)&c->d_tasks,
-                      (void **)&c->d_special, (void **)&c->d_partials, (void **)&c->d_red};
+                      (void **)&c->d_special, (void **)&c->d_flags, (void **)&c->d_partials, (void **)&c->d_red};
     for (void **p : owned)
         if (*p) {
             (void)hipFree(*p);
@@ -313,6 +314,12 @@ int allocate_device(ptrt_ctx *c)
         plain.insert(plain.end(), special.begin(), special.end());
         HIPCHK(c, hipMalloc(&c->d_tasks, sizeof(int4) * plain.size()));
         HIPCHK(c, hipMemcpy(c->d_tasks, plain.data(), sizeof(int4) * plain.size(), hipMemcpyHostToDevice));
+    }
+    if (c->lattice == PTRT_D3Q19 && c->has_mask && storage_bytes(c->storage) >= 4 && !c->d_tasks) {
+        HIPCHK(c, hipMalloc(&c->d_flags, sizeof(unsigned) * (size_t)c->N));
+        hipLaunchKernelGGL(k_link_flags<D3Q19>, node_grid(c->N), dim3(256), 0, c->stream, c->d_mask, c->geo,
+                           node_range(0, c->N), c->d_flags);
+        HIPCHK(c, hipGetLastError());
     }
     if (c->lattice == PTRT_D2Q9) {
         const int rc = plan_tiles(c);
@@ -531,8 +538,10 @@ void launch_step(ptrt_ctx *c, hipStream_t s)
 // Enqueue n steps: pairs in one pass where the configuration allows it.
 void launch_steps(ptrt_ctx *c, hipStream_t s, int n)
 {
+    const int call_steps = n;
     while (n >= 2 && c->steps_per_pass == 2) {
-        const StepLaunch a = step_args(c, s);
+        StepLaunch a = step_args(c, s);
+        a.call_steps = call_steps;
         bool two = false;
         double bytes = 0.0;
         if (c->lattice == PTRT_D2Q9) two = launch_step2_d2q9(a, &bytes);
@@ -561,6 +570,7 @@ StepLaunch step_args(const ptrt_ctx *c, hipStream_t s)
         a.n_special = c->n_special;
         a.masked_rows = c->masked_rows;
     }
+    a.link_flags = c->d_flags;
     a.g = geom(c);
     a.tau_plus = c->tau_plus;
     a.Lambda = c->Lambda;
@@ -1097,6 +1107,7 @@ int ptrt_destroy(ptrt_ctx *c)
     if (c->d_near) (void)hipFree(c->d_near);
     if (c->d_tasks) (void)hipFree(c->d_tasks);
     if (c->d_special) (void)hipFree(c->d_special);
+    if (c->d_flags) (void)hipFree(c->d_flags);
     for (auto &gx : c->graph)
         if (gx) (void)hipGraphExecDestroy(gx);
     if (c->capture_stream) (void)hipStreamDestroy(c->capture_stream);

@@ -35,6 +35,9 @@ struct StepLaunch {
     const int4 *tasks_plain = nullptr, *tasks_special = nullptr;
     int n_plain = 0, n_special = 0;
     long long masked_rows = 0;
+    // D3Q19 with solids: link flags per node (march3d.hpp)
+    const unsigned *link_flags = nullptr;
+    int call_steps = 0; // steps of the call that this launch is part of
 };
 
 void launch_step_d2q9(const StepLaunch &a);
@@ -182,8 +185,12 @@ bool step2_3d_task_lists(const Geom &g, const uint8_t *near, std::vector<int4> &
     }
 }
 
-// Whether a pair of steps without solids runs the march of march3d.hpp.
-// Measured, us a step, before -> march: where k_step2 (nx a multiple of 64)
+// Steps of a call from which on lattices with solids take the march; shorter
+// calls keep one step per pass, as ptrt_set_steps_per_pass documents.
+constexpr int MARCH_SOLID_MIN_STEPS = 8;
+
+// Whether a pair of steps runs the march of march3d.hpp.  Measured, us a
+// step, before -> march: without solids, where k_step2 (nx a multiple of 64)
 // ran before, the march is faster below 800 000 nodes, whose few columns
 // leave k_step2's longer chains exposed (64^3 FP32 13.7 -> 8.2, FP64
 // 20.0 -> 13.8; 192 x 64 x 64 16.4 -> 14.5; 64 x 128 x 128 17.0 -> 22.2).
@@ -192,30 +199,38 @@ bool step2_3d_task_lists(const Geom &g, const uint8_t *near, std::vector<int4> &
 // 300^3 FP32 970 -> 626, FP64 1584 -> 970) unless its rows are mostly idle
 // lanes: at least 24 columns, and in FP32 at least 42 once the lattice is
 // too large for the last-level cache to hide the others' loads (130^3, 44
-// columns, 67.4 -> 65.5).
+// columns, 67.4 -> 65.5).  With solids (walls or a block over 1/8 of each
+// axis; one step per pass before) FP64 gains throughout (128 x 96 x 96 63 ->
+// 54, 100 x 84 x 92 44 -> 30, 200^3 470 -> 319, 256^3 854 -> 609), FP32 with
+// rows mostly full below 6 million nodes (50 x 60 x 70 10.8 -> 9.6, 180 x
+// 160 x 170 156 -> 134; 128 x 96 x 96, 43 columns, 28.5 -> 32.3, 200^3 241
+// -> 284: its flags take the registers of eight waves per SIMD).
 inline bool march_applies(const StepLaunch &a)
 {
     const Geom &g = a.g;
-    if ((a.storage != PTRT_F32 && a.storage != PTRT_F64) || a.model != MODEL_PTRT || a.has_mask) return false;
+    if ((a.storage != PTRT_F32 && a.storage != PTRT_F64) || a.model != MODEL_PTRT) return false;
     const size_t elem = storage_bytes(a.storage);
     // 32-bit offsets inside a plane of whole layout tiles
     if (g.ny % (1 << g.lr) != 0 || (double)(g.ny >> g.lr) * (double)g.tile * (double)elem >= 4294967296.0)
         return false;
     const double nodes = (double)g.nx * g.ny * g.nz;
-    if (g.nx % Step2Shape<D3Q19, float>::BX == 0 && g.ny >= Step2Shape<D3Q19, float>::BY) return nodes < 8e5;
     const int cols = march_cols(g.nx);
+    if (a.has_mask)
+        return a.link_flags && a.call_steps >= MARCH_SOLID_MIN_STEPS && nodes >= 8e4 &&
+               (elem == 8 ? cols >= 24 : cols >= 48 && nodes <= 6e6);
+    if (g.nx % Step2Shape<D3Q19, float>::BX == 0 && g.ny >= Step2Shape<D3Q19, float>::BY) return nodes < 8e5;
     return nodes >= 8e4 && cols >= (elem == 4 && nodes > 1.5e6 ? 42 : 24);
 }
 
 // Planes per chunk: as step2_3d_zc, down to single planes (a small lattice
 // takes short chains over many workgroups).
-template <class S, class SH>
+template <class S, class SH, bool SOLID>
 int march_zc(const Geom &g)
 {
     static const int resident = [] {
         int per_cu = 0, dev = 0, cus = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &per_cu, reinterpret_cast<const void *>(&k_march3d<S, SH>), 64 * SH::AY, 0) != hipSuccess ||
+                &per_cu, reinterpret_cast<const void *>(&k_march3d<S, SH, SOLID>), 64 * SH::AY, 0) != hipSuccess ||
             hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
             per_cu <= 0 || cus <= 0)
@@ -245,25 +260,30 @@ void launch_march(const StepLaunch &a, double *pass_bytes)
     using C = typename Codec<S>::compute;
     const Coef<D3Q19, C> r = make_coef<D3Q19, C>(a.tau_plus, a.Lambda, a.force);
     const double nodes = (double)a.g.nx * a.g.ny * a.g.nz;
-    if (pass_bytes) *pass_bytes = 2.0 * nodes * D3Q19::Q * sizeof(S);
-    auto go = [&](auto sh) {
+    if (pass_bytes) *pass_bytes = nodes * (2.0 * D3Q19::Q * sizeof(S) + (a.has_mask ? 1.0 : 0.0));
+    auto go = [&](auto sh, auto mc) {
         using SH = decltype(sh);
-        const int cols = march_cols(a.g.nx), zc = march_zc<S, SH>(a.g);
+        constexpr bool SOLID = decltype(mc)::value;
+        const int cols = march_cols(a.g.nx), zc = march_zc<S, SH, SOLID>(a.g);
         const dim3 grid((a.g.nx + cols - 1) / cols, (a.g.ny + SH::BY - 1) / SH::BY, (a.g.nz + zc - 1) / zc);
-        hipLaunchKernelGGL((k_march3d<S, SH>), grid, dim3(64 * SH::AY), 0, a.stream, (const S *)a.src,
-                           (S *)a.dst, a.g, r, zc, cols);
+        hipLaunchKernelGGL((k_march3d<S, SH, SOLID>), grid, dim3(64 * SH::AY), 0, a.stream, (const S *)a.src,
+                           (S *)a.dst, a.link_flags, a.g, r, zc, cols);
     };
+    if (a.has_mask) {
+        go(MarchShape<S, 6>{}, std::true_type{});
+        return;
+    }
     // six rows share their halo better; on large FP32 lattices more rows in
     // flight evict halo lines before the neighbouring columns read them
     // (us a step, six / four rows: 100 x 84 x 92 16.2 / 19.8, 186^3 152 /
     // 148, 300^3 729 / 626; FP64 300^3 971 / 975)
     if constexpr (sizeof(S) == 4) {
         if (nodes > 6e6) {
-            go(MarchShape<S, 4>{});
+            go(MarchShape<S, 4>{}, std::false_type{});
             return;
         }
     }
-    go(MarchShape<S, 6>{});
+    go(MarchShape<S, 6>{}, std::false_type{});
 }
 
 template <class L>

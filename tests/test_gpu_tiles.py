@@ -1,5 +1,5 @@
 """D2Q9 passes of several steps on tiles in LDS (calls of eight steps and
-more): the populations equal those of one step per pass bit for bit, for
+more) and the D3Q19 march: the populations equal those of one step per pass bit for bit, for
 every storage type, with solids, open x, Scheme I and in a batch.  The sizes
 put the lattice edge, the periodic wrap, solids and the open boundaries at
 every place of a tile, down to lattices smaller than a tile's halo."""
@@ -171,3 +171,37 @@ def test_d3q19_march(shape, storage):
             assert G.last_pass()[0] == spp
             got.append(G.populations())
     assert np.array_equal(got[0], got[1])
+
+
+# the same with solids, in calls of eight steps and more: walls on the y seam,
+# a block, solids on the corner of the box, scattered ones (every kind of
+# link, on every plane of a chunk and row of a workgroup)
+@pytest.mark.parametrize("storage", ["f32", "f64"])
+@pytest.mark.parametrize("kind", ["walls", "block", "corner", "random"])
+@pytest.mark.parametrize("shape", [(47, 45, 48), (3, 600, 62), (90, 85, 101), (64, 50, 64)])
+def test_d3q19_march_solids(shape, kind, storage):
+    print_case("D3Q19 march with solids against single steps", shape, kind, storage)
+    nz, ny, nx = shape
+    mask = np.zeros(shape, dtype=np.uint8)
+    if kind == "walls":
+        mask[:, 0] = mask[:, -1] = 1
+    if kind == "block":
+        mask[nz // 3:nz // 2 + 1, ny // 3:ny // 2, nx // 4:nx // 2] = 1
+    if kind == "corner":
+        mask[-1:, -2:, -2:] = mask[:1, :2, :1] = mask[nz // 2, ny // 2, nx // 2] = 1
+    if kind == "random":
+        mask[:] = np.random.default_rng(nz).random(shape) < 0.12
+    rho, u = I.random_fields(np.random.default_rng(nx), shape, umax=0.04)
+    got, passes = [], []
+    for spp in (1, 2):
+        with P.Lattice(P.PTRT_D3Q19, nx, ny, nz, 0.64, 0.2, force=[3e-6, -1e-6, 2e-6], storage=storage,
+                       solid_mask=mask, steps_per_pass=spp) as G:
+            G.init_equilibrium(rho, u)
+            G.step(9)
+            G.step(8)
+            passes.append(G.last_pass()[0])
+            got.append(G.populations())
+    fluid = np.broadcast_to(mask == 0, got[0].shape)
+    assert np.array_equal(got[0][fluid], got[1][fluid])
+    # 64 x 64 x 50 falls into strips of 32 columns: one step per pass in FP32
+    assert passes == [1, 1 if storage == "f32" and nx == 64 else 2]
