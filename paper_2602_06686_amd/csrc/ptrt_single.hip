@@ -315,8 +315,14 @@ int allocate_device(ptrt_ctx *c)
         HIPCHK(c, hipMalloc(&c->d_tasks, sizeof(int4) * plain.size()));
         HIPCHK(c, hipMemcpy(c->d_tasks, plain.data(), sizeof(int4) * plain.size(), hipMemcpyHostToDevice));
     }
-    if (c->lattice == PTRT_D3Q19 && c->has_mask && storage_bytes(c->storage) >= 4 && !c->d_tasks) {
-        HIPCHK(c, hipMalloc(&c->d_flags, sizeof(unsigned) * (size_t)c->N));
+    if (c->lattice == PTRT_D3Q19 && c->has_mask && !c->d_tasks && march_lattice(c->geo, c->storage, true)) {
+        // without memory for them the lattice keeps one step per pass
+        if (hipMalloc(&c->d_flags, sizeof(unsigned) * (size_t)c->N) != hipSuccess) {
+            (void)hipGetLastError();
+            c->d_flags = nullptr;
+        }
+    }
+    if (c->d_flags) {
         hipLaunchKernelGGL(k_link_flags<D3Q19>, node_grid(c->N), dim3(256), 0, c->stream, c->d_mask, c->geo,
                            node_range(0, c->N), c->d_flags);
         HIPCHK(c, hipGetLastError());

@@ -189,8 +189,8 @@ bool step2_3d_task_lists(const Geom &g, const uint8_t *near, std::vector<int4> &
 // calls keep one step per pass, as ptrt_set_steps_per_pass documents.
 constexpr int MARCH_SOLID_MIN_STEPS = 8;
 
-// Whether a pair of steps runs the march of march3d.hpp.  Measured, us a
-// step, before -> march: without solids, where k_step2 (nx a multiple of 64)
+// Lattices on which a pair of steps runs the march of march3d.hpp.
+// Measured, us a step, before -> march: without solids, where k_step2 (nx a multiple of 64)
 // ran before, the march is faster below 800 000 nodes, whose few columns
 // leave k_step2's longer chains exposed (64^3 FP32 13.7 -> 8.2, FP64
 // 20.0 -> 13.8; 192 x 64 x 64 16.4 -> 14.5; 64 x 128 x 128 17.0 -> 22.2).
@@ -205,21 +205,24 @@ constexpr int MARCH_SOLID_MIN_STEPS = 8;
 // rows mostly full below 6 million nodes (50 x 60 x 70 10.8 -> 9.6, 180 x
 // 160 x 170 156 -> 134; 128 x 96 x 96, 43 columns, 28.5 -> 32.3, 200^3 241
 // -> 284: its flags take the registers of eight waves per SIMD).
-inline bool march_applies(const StepLaunch &a)
+inline bool march_lattice(const Geom &g, int storage, bool solids)
 {
-    const Geom &g = a.g;
-    if ((a.storage != PTRT_F32 && a.storage != PTRT_F64) || a.model != MODEL_PTRT) return false;
-    const size_t elem = storage_bytes(a.storage);
+    if (storage != PTRT_F32 && storage != PTRT_F64) return false;
+    const size_t elem = storage_bytes(storage);
     // 32-bit offsets inside a plane of whole layout tiles
     if (g.ny % (1 << g.lr) != 0 || (double)(g.ny >> g.lr) * (double)g.tile * (double)elem >= 4294967296.0)
         return false;
     const double nodes = (double)g.nx * g.ny * g.nz;
     const int cols = march_cols(g.nx);
-    if (a.has_mask)
-        return a.link_flags && a.call_steps >= MARCH_SOLID_MIN_STEPS && nodes >= 8e4 &&
-               (elem == 8 ? cols >= 24 : cols >= 48 && nodes <= 6e6);
+    if (solids) return nodes >= 8e4 && (elem == 8 ? cols >= 24 : cols >= 48 && nodes <= 6e6);
     if (g.nx % Step2Shape<D3Q19, float>::BX == 0 && g.ny >= Step2Shape<D3Q19, float>::BY) return nodes < 8e5;
     return nodes >= 8e4 && cols >= (elem == 4 && nodes > 1.5e6 ? 42 : 24);
+}
+
+inline bool march_applies(const StepLaunch &a)
+{
+    if (a.model != MODEL_PTRT || !march_lattice(a.g, a.storage, a.has_mask)) return false;
+    return !a.has_mask || (a.link_flags && a.call_steps >= MARCH_SOLID_MIN_STEPS);
 }
 
 // Planes per chunk: as step2_3d_zc, down to single planes (a small lattice
