@@ -15,21 +15,22 @@
 // in its own slot ibar and leaves h*_i in slot i.  With a solid source (or
 // the inlet wall) the even step uses its own slot ibar in place of the
 // source's slot i: the value that bounces back, and the place where the
-// following odd step looks for it.  Columns and rows past the region
-// the steps compute values that no later step of the core reads, in slots of their own
-// (the slot map is one to one on the linear node index), so no lane is
-// masked before the last store.
+// following odd step looks for it.  Lanes and rows past a
+// step's region compute values that no later step of the core reads, in
+// slots of their own (the slot map is one to one on the linear node index),
+// so no lane is masked before the last store.
 //
 // What bounds it and why this shape: instruction issue.  A wave updates a
 // row of 64 nodes with about 105 VALU instructions, 9 LDS reads and 9 LDS
 // writes with compile-time offsets from one address register (VALU busy
-// about 80 % of the time at 2048^2); HBM sees the state once per pass.  Two
+// 94 % of the time at 2048^2 in FP32, 48 % in FP64, whose registers leave
+// four waves per SIMD); HBM sees the state once per pass.  Two
 // workgroups per CU, one computing while the other waits for its first
 // step's loads.  Measured against the passes of two steps along rows
-// (k_step2_2d; us a step, before -> after): 2048^2 FP32 36.7 -> 18.0, FP64
-// 64.8 -> 40.1; 4096^2 FP32 156 -> 74, FP16 (one step a pass before)
-// 94 -> 79; 509 x 381 FP32 3.69 -> 1.67; 64^2 FP64 2.32 -> 0.93; 512
-// lattices of 32 to 512 nodes a side FP32 407 -> 212.
+// (k_step2_2d; us a step, before -> after): 2048^2 FP32 36.7 -> 17.7,
+// FP64 64.8 -> 36.5; 4096^2 FP32 156 -> 71, FP16 (one step a pass before)
+// 94 -> 78; 509 x 381 FP32 3.69 -> 1.70; 64^2 FP64 2.32 -> 0.93; 512
+// lattices of 32 to 512 nodes a side FP32 407 -> 178.
 #pragma once
 
 #include "step2.hpp"

@@ -46,19 +46,20 @@ inline int tile_core(int n, int most)
 // for the lattices of one launch, or none where the passes of one and two
 // steps are estimated faster.
 //
-// A tile pass costs a launch (c0) and rounds of the workgroups a CU holds:
-// a round takes its issue time (rows of 64 nodes over all steps, q each,
-// and mem for the first step's loads), or the dependent chain of one workgroup (lat per iteration of its waves, plus beta of its
-// own issue time) if that is longer; the bytes it moves add their time at
-// bw.  The constants are those that choose best among the shapes with T =
-// 3 ... 8 timed on fourteen lattices and batches (64^2 ... 4096^2, FP32 and
-// FP64): the fastest pass at twelve, within 6 % (700^2) and 2 % of it at the
-// others.  The earlier passes take about 2 us a launch and run at 113 (FP32), 64 (FP64)
-// and 180 (16 bits) nodes a ns over rows padded to whole strips; they stay
-// faster on lattices of one or two rows, where a tile is mostly halo
-// (600000 x 1 FP32 6.2 us a step against 18.5), and for stochastic rounding
-// on large lattices, whose nine rounded stores double the issue time
-// (2048^2 FP16 23 us against 38).
+// A tile pass costs a launch (c0) and rounds of the workgroups a CU holds: a
+// round takes its issue time (rows of 64 nodes over all steps, q each, and
+// mem for the first step's loads), or the dependent chain of one workgroup
+// (lat per iteration of its waves, plus beta of its own issue time) if that
+// is longer; the bytes it moves add their time at bw. The constants are
+// those that choose best among the shapes with T = 3 ... 8 timed on fourteen
+// lattices and batches (64^2 ... 4096^2, FP32 and FP64): the fastest pass at
+// twelve, within 6 % (700^2) and 2 % of it at the others. The earlier passes
+// take about 2 us a launch and run at 113 (FP32), 64 (FP64) and 180 (16
+// bits) nodes a ns over rows padded to whole strips; they stay faster on
+// lattices of one or two rows, where a tile is mostly halo (600000 x 1 FP32
+// 6.2 us a step against 18.5), and for stochastic rounding on large
+// lattices, whose nine rounded stores double the issue time (2048^2 FP16 23
+// us against 38).
 inline TilePlan choose_tile_plan(int storage, const std::vector<std::pair<int, int>> &sizes)
 {
     const size_t elem = storage_bytes(storage);
