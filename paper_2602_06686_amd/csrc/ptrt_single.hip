@@ -165,6 +165,7 @@ void release_device(ptrt_ctx *c)
             *p = nullptr;
         }
     c->n_plain = c->n_special = 0;
+    c->tile = TilePlan{};
 }
 
 int allocate_device(ptrt_ctx *c);
@@ -184,7 +185,8 @@ int ensure_allocated(ptrt_ctx *c)
 }
 
 // The D2Q9 tile plan, and which tiles a solid or an open x boundary is in
-// reach of.
+// reach of.  The handle takes the plan once its flags are in place: without
+// them a pass would treat every tile as periodic fluid.
 int plan_tiles(ptrt_ctx *c)
 {
     TilePlan p = choose_tile_plan(c->storage, {{c->nx, c->ny}});
@@ -193,8 +195,10 @@ int plan_tiles(ptrt_ctx *c)
     p.ch = tile_core(c->ny, p.ch);
     p.tiles_x = (c->nx + p.cw - 1) / p.cw;
     p.tiles = p.tiles_x * ((c->ny + p.ch - 1) / p.ch);
-    c->tile = p;
-    if (!c->has_mask && !c->open) return PTRT_OK;
+    if (!c->has_mask && !c->open) {
+        c->tile = p;
+        return PTRT_OK;
+    }
     std::vector<uint8_t> special(p.tiles, 0);
     const int reach = p.T; // the region and one node around it
     if (c->has_mask) {
@@ -212,6 +216,7 @@ int plan_tiles(ptrt_ctx *c)
         }
     HIPCHK(c, hipMalloc(&c->d_special, special.size()));
     HIPCHK(c, hipMemcpy(c->d_special, special.data(), special.size(), hipMemcpyHostToDevice));
+    c->tile = p;
     return PTRT_OK;
 }
 

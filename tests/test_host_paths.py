@@ -1,0 +1,68 @@
+"""The host code of libptrt without a GPU: a stand-in for the HIP runtime
+(tests/host/recorder.cpp) records which kernels a call launches, with which
+grids, and makes allocations fail.  Each case is a script of its own process
+(tests/host/library.py)."""
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+from conftest import ROOT
+
+HOST = os.path.join(ROOT, "tests", "host")
+LIB = os.path.join(ROOT, "paper_2602_06686_amd", "libptrt.so")
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    if not (shutil.which("g++") and os.path.exists(LIB)):
+        pytest.skip("needs g++ and the built library")
+    out = tmp_path_factory.mktemp("host")
+    recorder = str(out / "recorder.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-pthread",
+                    os.path.join(HOST, "recorder.cpp"), "-o", recorder], check=True)
+
+    def script(text, timeout=120):
+        path = str(out / "script.py")
+        with open(path, "w") as fh:
+            fh.write(text)
+        res = subprocess.run([sys.executable, os.path.join(HOST, "library.py"), recorder, LIB, path],
+                             capture_output=True, text=True, timeout=timeout)
+        assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-2000:]
+        return res.stdout
+
+    return script
+
+
+@pytest.mark.parametrize("boundary", ["solids", "open"])
+def test_storage_after_a_failed_allocation(run, boundary):
+    """Whichever allocation of the first init fails, the handle then takes
+    another storage type and runs the passes of that type: no tile pass of the
+    failed attempt's plan, which would not know of solids and open x."""
+    run(f"""
+mask = bytearray(2048 * 2048)
+mask[0] = 1
+for k in range(1, 20):
+    h = create(D2Q9, 2048, 2048, 1, F64, bytes(mask) if {boundary == "solids"} else None)
+    if {boundary == "open"}:
+        ok(L.ptrt_set_open_x(h, C.c_double(0.01), C.c_double(1.0)), h)
+    R.rec_fail_device(k)
+    rc = L.ptrt_init_equilibrium(h, None, None)
+    R.rec_fail_device(0)
+    if rc == 0:
+        break
+    assert rc in (ENOMEM, EDEVICE)
+    assert L.ptrt_set_storage(h, F16_SR) == 0
+    init(h)
+    assert set(kernels(h, 10)) == {{"k_step"}}, (k, launches())
+    ok(L.ptrt_destroy(h), h)
+assert k > 5
+# the same handle without a failure: tile passes, with the flags of their tiles
+ok(L.ptrt_destroy(h), h)
+h = create(D2Q9, 2048, 2048, 1, F64, bytes(mask))
+init(h)
+assert set(kernels(h, 10)) == {{"k_tile_2d"}}
+assert all(R.rec_pointer(i, 4) for i in range(R.rec_launches()))
+""")
