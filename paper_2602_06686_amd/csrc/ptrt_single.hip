@@ -546,10 +546,10 @@ void launch_step(ptrt_ctx *c, hipStream_t s)
     c->cur ^= 1;
 }
 
-// Enqueue n steps: pairs in one pass where the configuration allows it.
-void launch_steps(ptrt_ctx *c, hipStream_t s, int n)
+// Enqueue n steps of a call of call_steps: pairs in one pass where the
+// configuration allows it.
+void launch_steps(ptrt_ctx *c, hipStream_t s, int n, int call_steps)
 {
-    const int call_steps = n;
     while (n >= 2 && c->steps_per_pass == 2) {
         StepLaunch a = step_args(c, s);
         a.call_steps = call_steps;
@@ -638,7 +638,8 @@ int capture_graph(ptrt_ctx *c, int parity)
     c->cur = parity;
     hipGraph_t gr = nullptr;
     HIPCHK(c, hipStreamBeginCapture(c->capture_stream, hipStreamCaptureModeThreadLocal));
-    launch_steps(c, c->capture_stream, GRAPH_STEPS);
+    static_assert(GRAPH_STEPS >= MARCH_SOLID_MIN_STEPS, "a call with a replay is a long one");
+    launch_steps(c, c->capture_stream, GRAPH_STEPS, GRAPH_STEPS);
     hipError_t e = hipStreamEndCapture(c->capture_stream, &gr);
     c->cur = saved;
     if (e != hipSuccess) return fail_hip(c, PTRT_EDEVICE, std::string("graph capture: ") + hipGetErrorString(e));
@@ -778,8 +779,10 @@ void launch_tile_pass(ptrt_ctx *c, int T)
     c->last_pass_bytes = ptrt_bytes_per_node(c) * (double)c->N;
 }
 
-// Enqueue n steps: tile passes, graph replays where captured, else launches.
-int advance(ptrt_ctx *c, int n)
+// Enqueue n steps of a call of call_steps (the rest comes before or after
+// divergence checks): tile passes, graph replays where captured, else
+// launches.
+int advance(ptrt_ctx *c, int n, int call_steps)
 {
     if (tiles_apply(c, n)) n = tile_passes(c->tile, n, [&](int T) { launch_tile_pass(c, T); });
     if (c->use_graph)
@@ -791,7 +794,7 @@ int advance(ptrt_ctx *c, int n)
             HIPCHK(c, hipGraphLaunch(c->graph[c->cur], c->stream));
             n -= GRAPH_STEPS;
         }
-    launch_steps(c, c->stream, n);
+    launch_steps(c, c->stream, n, call_steps);
     return PTRT_OK;
 }
 
@@ -1004,11 +1007,12 @@ int ptrt_step(ptrt_ctx *c, int n)
                         "the divergence check found a non-finite population at step " +
                             std::to_string(c->diverged_at) + "; no steps enqueued");
     }
+    const int call_steps = n;
     while (n > 0) {
         int m = n;
         if (c->check_every > 0)
             m = (int)std::min<long long>(n, c->check_every - c->t % c->check_every);
-        int rc = advance(c, m);
+        int rc = advance(c, m, call_steps);
         if (rc != PTRT_OK) return rc;
         c->t += m;
         n -= m;

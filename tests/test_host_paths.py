@@ -66,3 +66,27 @@ init(h)
 assert set(kernels(h, 10)) == {{"k_tile_2d"}}
 assert all(R.rec_pointer(i, 4) for i in range(R.rec_launches()))
 """)
+
+
+@pytest.mark.parametrize("steps", [8, 9, 20, 21, 23, 27, 47])
+def test_march_covers_the_remainder_after_graph_replays(run, steps):
+    """A call of eight steps or more on a D3Q19 lattice with solids takes the
+    march for all its pairs, those after the replayed graphs of 20 steps too."""
+    run(f"""
+h = create(D3Q19, 48, 45, 47, F64, bytes([1]) + bytes(48 * 45 * 47 - 1))
+init(h)
+assert kernels(h, {steps}) == ["k_march3d"] * {steps // 2} + ["k_step"] * {steps % 2}
+assert last_pass(h) == {2 - steps % 2}
+assert kernels(h, 7) == ["k_step"] * 7 and last_pass(h) == 1
+""")
+
+
+def test_march_between_divergence_checks(run):
+    """The check splits a call; its pieces are still parts of a long call."""
+    run("""
+h = create(D3Q19, 48, 45, 47, F64, bytes([1]) + bytes(48 * 45 * 47 - 1))
+init(h)
+ok(L.ptrt_set_divergence_check(h, 4), h)
+assert kernels(h, 12) == ["k_march3d", "k_march3d", "k_check_finite"] * 3
+assert kernels(h, 4) == ["k_step"] * 4 + ["k_check_finite"]
+""")
