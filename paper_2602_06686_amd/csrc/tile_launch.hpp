@@ -106,6 +106,9 @@ inline TilePlan choose_tile_plan(int storage, const std::vector<std::pair<int, i
                     region += (double)k * (cw + 2 * (T - 1)) * (ch + 2 * (T - 1));
                     chain = std::max(chain, its);
                 }
+                // a launch has fewer than 2^32 threads (rows of hundreds of
+                // millions of nodes, few of them)
+                if (tiles * 64 * SH::NW >= 1LL << 32) continue;
                 const double issue = wave_rows / (double)tiles * q, alone = chain * lat + beta * issue;
                 const long long per_cu = (tiles + CUS - 1) / CUS, rounds = (per_cu + occ - 1) / occ;
                 const long long last = per_cu - (rounds - 1) * occ;

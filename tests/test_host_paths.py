@@ -90,3 +90,18 @@ ok(L.ptrt_set_divergence_check(h, 4), h)
 assert kernels(h, 12) == ["k_march3d", "k_march3d", "k_check_finite"] * 3
 assert kernels(h, 4) == ["k_step"] * 4 + ["k_check_finite"]
 """)
+
+
+@pytest.mark.parametrize("storage", ["F32", "F64", "F16"])
+def test_no_launch_beyond_the_thread_limit(run, storage):
+    """Rows so long and few that a tile per core would need 2^32 threads or
+    more in a launch: the passes of before run."""
+    run(f"""
+for nx, ny in ((300000000, 7), (400000000, 5), (470000000, 4)):
+    h = C.c_void_p()
+    ok(L.ptrt_create(D2Q9, nx, ny, 1, C.c_double(0.7), C.c_double(0.25), None, None, C.byref(h)), None)
+    if L.ptrt_set_storage(h, {storage}) == 0:
+        init(h)
+        step(h, 10)
+    ok(L.ptrt_destroy(h), h)
+""")
