@@ -120,8 +120,8 @@ struct BDiag {
     int first;
 };
 
-// Partials of block b of the batch, as k_gather computes them for its
-// lattice.  One launch for all lattices (512 lattices: 4.4 -> 0.4 ms against
+// Partials of block b (from first_block on) of the batch, as k_gather computes
+// them for its lattice.  One launch for all lattices (512 lattices: 4.4 -> 0.4 ms against
 // two launches each); the block finds its lattice by bisection of first[],
 // nine scalar loads that the other blocks on the CU cover.
 template <class S>
@@ -129,9 +129,9 @@ __global__ void __launch_bounds__(256)
 k_batch_gather(const S *__restrict__ src, const uint8_t *__restrict__ mask,
                const uint8_t *__restrict__ near,
                const BInst<typename Codec<S>::compute> *__restrict__ inst,
-               const BDiag *__restrict__ diag, int count, double2 *__restrict__ partials)
+               const BDiag *__restrict__ diag, int count, int first_block, double2 *__restrict__ partials)
 {
-    const int b = (int)blockIdx.x;
+    const int b = first_block + (int)blockIdx.x;
     int k = 0;
     for (int hi = count; hi - k > 1;) {
         const int mid = (k + hi) >> 1;
@@ -165,13 +165,23 @@ k_batch_gather(const S *__restrict__ src, const uint8_t *__restrict__ mask,
     if (threadIdx.x == 0 && threadIdx.y == 0) partials[b] = make_double2(m, e);
 }
 
-// Workgroup k sums the partials of lattice k in k_finalize's order.
+// Workgroup k (from lattice `base` on) sums the partials of lattice k in
+// k_finalize's order.
 __global__ void __launch_bounds__(1024)
-k_batch_finalize(const double2 *__restrict__ partials, const BDiag *__restrict__ diag,
+k_batch_finalize(const double2 *__restrict__ partials, const BDiag *__restrict__ diag, int base,
                  double *__restrict__ out)
 {
-    const int k = (int)blockIdx.x, first = diag[k].first;
+    const int k = base + (int)blockIdx.x, first = diag[k].first;
     sum_partials(partials + first, diag[k + 1].first - first, out + 2 * k);
+}
+
+// f(first, count) for pieces of n workgroups that one launch can take: it
+// has fewer than 2^32 threads.
+template <class F>
+void for_launches(int n, int threads, F &&f)
+{
+    const int most = 0x7fffffff / threads;
+    for (int first = 0; first < n; first += std::min(most, n - first)) f(first, std::min(most, n - first));
 }
 
 thread_local std::string g_batch_create_error = "no error";
@@ -1123,14 +1133,18 @@ int ptrt_batch_diagnostics(ptrt_batch *b, double *mass, double *ke)
     const double *r = (const double *)stage.ptr;
     dispatch_storage(b->storage, false, [&](auto st, auto) -> int {
         using S = typename decltype(st)::type;
-        hipLaunchKernelGGL((k_batch_gather<S>), dim3(b->nparts), dim3(BLK_X, BLK_Y, 1), 0, b->stream,
-                           (const S *)b->buf[b->cur], b->d_mask, b->d_near,
-                           (const BInst<typename Codec<S>::compute> *)b->d_inst, b->d_diag, b->count,
-                           b->d_partials);
+        for_launches(b->nparts, BLK_X * BLK_Y, [&](int first, int n) {
+            hipLaunchKernelGGL((k_batch_gather<S>), dim3(n), dim3(BLK_X, BLK_Y, 1), 0, b->stream,
+                               (const S *)b->buf[b->cur], b->d_mask, b->d_near,
+                               (const BInst<typename Codec<S>::compute> *)b->d_inst, b->d_diag, b->count,
+                               first, b->d_partials);
+        });
         return PTRT_OK;
     });
-    hipLaunchKernelGGL(k_batch_finalize, dim3(b->count), dim3(1024), 0, b->stream, b->d_partials, b->d_diag,
-                       (double *)stage.ptr);
+    for_launches(b->count, 1024, [&](int first, int n) {
+        hipLaunchKernelGGL(k_batch_finalize, dim3(n), dim3(1024), 0, b->stream, b->d_partials, b->d_diag,
+                           first, (double *)stage.ptr);
+    });
     hipError_t e = hipGetLastError();
     const hipError_t waited = hipStreamSynchronize(b->stream);
     if (e == hipSuccess) e = waited;

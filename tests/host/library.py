@@ -57,8 +57,9 @@ def launches():
     out = []
     for k in range(R.rec_launches()):
         name = R.rec_name(k).decode()
-        m = re.match(r"(?:void )?ptrt::(\w+)(?:<(.*)>)?\(", name.replace("(anonymous namespace)::", ""))
-        m_raw = re.match(r"_ZN4ptrt(\d+)(.*)", name)  # types that the demangler does not know
+        m = re.match(r"(?:void )?(?:ptrt|\(anonymous namespace\))::(\w+)(?:<(.*)>)?\(", name)
+        # types that the demangler does not know
+        m_raw = re.match(r"_ZN(?:4ptrt|12_GLOBAL__N_1)(\d+)(.*)", name)
         shape = (C.c_uint * 6)()
         R.rec_shape(k, shape)
         if m:

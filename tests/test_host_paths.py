@@ -105,3 +105,20 @@ for nx, ny in ((300000000, 7), (400000000, 5), (470000000, 4)):
         step(h, 10)
     ok(L.ptrt_destroy(h), h)
 """)
+
+
+def test_batch_diagnostics_beyond_one_launch(run):
+    """Blocks of a batch whose one launch would have 2^32 threads or more
+    (lattices of one column: 64 times the threads of their nodes) are taken
+    in several, each block once."""
+    run("""
+rc, b = batch([(1, 262140)] * 257, F16)
+assert rc == 0, L.ptrt_batch_last_error(None)
+mass, energy = (C.c_double * 257)(), (C.c_double * 257)()
+R.rec_reset()
+assert L.ptrt_batch_diagnostics(b, mass, energy) == 0, L.ptrt_batch_last_error(b)
+gather = [l for l in launches() if l[0] == "k_batch_gather"]
+assert sum(l[2][0] for l in gather) == 257 * 65535
+assert [l[2][0] for l in launches() if l[0] == "k_batch_finalize"] == [257]
+L.ptrt_batch_destroy(b)
+""")
