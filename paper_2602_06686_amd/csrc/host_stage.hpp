@@ -9,6 +9,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <unistd.h>
 
 #include <algorithm>
 #include <atomic>
@@ -34,11 +35,19 @@ public:
         static std::weak_ptr<HostPool> *w = new std::weak_ptr<HostPool>;
         std::lock_guard<std::mutex> lock(*m);
         std::shared_ptr<HostPool> p = w->lock();
-        if (!p) *w = p = std::shared_ptr<HostPool>(new HostPool);
+        if (!p) *w = p = std::shared_ptr<HostPool>(new HostPool, &HostPool::release);
         return p;
     } catch (...) {
         return nullptr;
     }
+
+    // In a forked child the threads do not exist, and what they hold and wait
+    // for is as it was: the child leaves an inherited pool alone.
+    static void release(HostPool *p)
+    {
+        if (p->own_process()) delete p;
+    }
+    bool own_process() const { return getpid() == pid_; }
 
     ~HostPool()
     {
@@ -55,8 +64,8 @@ public:
     template <class F>
     void parallel(int n, const F &f)
     {
-        if (n > 1) start();
-        if (n <= 1 || threads_ == 0) {
+        if (n > 1 && own_process()) start();
+        if (n <= 1 || threads_ == 0 || !own_process()) {
             for (int i = 0; i < n; ++i) f(i);
             return;
         }
@@ -173,6 +182,7 @@ private:
         }
     }
 
+    const pid_t pid_ = getpid();
     std::mutex mutex_;
     std::condition_variable work_, idle_;
     Job *jobs_ = nullptr;

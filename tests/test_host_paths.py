@@ -122,3 +122,33 @@ assert sum(l[2][0] for l in gather) == 257 * 65535
 assert [l[2][0] for l in launches() if l[0] == "k_batch_finalize"] == [257]
 L.ptrt_batch_destroy(b)
 """)
+
+
+def test_handle_freed_in_a_forked_child(run):
+    """The host threads of the transfers do not exist in a forked child:
+    freeing the inherited handle there returns, and so does a read-back."""
+    run("""
+import os, time
+h = create(D3Q19, 128, 128, 96)
+init(h)
+rho = (C.c_double * (128 * 128 * 96))()
+for _ in range(4):
+    ok(L.ptrt_moments(h, rho, None), h)
+pid = os.fork()
+if pid == 0:
+    ok(L.ptrt_moments(h, rho, None), h)
+    ok(L.ptrt_moments(h, rho, None), h)
+    L.ptrt_destroy(h)
+    os._exit(7)
+for _ in range(100):
+    done, status = os.waitpid(pid, os.WNOHANG)
+    if done:
+        break
+    time.sleep(0.1)
+else:
+    os.kill(pid, 9)
+    os.waitpid(pid, 0)
+assert done and os.WEXITSTATUS(status) == 7
+ok(L.ptrt_moments(h, rho, None), h)
+L.ptrt_destroy(h)
+""")
