@@ -152,3 +152,32 @@ assert done and os.WEXITSTATUS(status) == 7
 ok(L.ptrt_moments(h, rho, None), h)
 L.ptrt_destroy(h)
 """)
+
+
+def test_threads_only_for_what_is_moved(run):
+    """A small handle that is read a few times starts no thread; one that is
+    read on and on, or a large one, as many as its pieces keep busy."""
+    run("""
+import os
+threads = lambda: len(os.listdir("/proc/self/task")) - 1
+most = min(15, len(os.sched_getaffinity(0)) - 1)
+n = 32 * 32 * 32
+rho, u = (C.c_double * n)(), (C.c_double * (3 * n))()
+h = create(D3Q19, 32, 32, 32)
+ok(L.ptrt_init_equilibrium(h, rho, u), h)       # 1 MB, four pieces
+for _ in range(5):
+    ok(L.ptrt_moments(h, rho, u), h)
+assert threads() == 0, threads()
+for _ in range(5):
+    ok(L.ptrt_moments(h, rho, u), h)
+assert threads() == min(3, most), threads()
+L.ptrt_destroy(h)
+assert threads() == 0
+n = 128 * 128 * 128
+rho, u = (C.c_double * n)(), (C.c_double * (3 * n))()
+h = create(D3Q19, 128, 128, 128)
+ok(L.ptrt_init_equilibrium(h, rho, u), h)
+assert threads() == most
+L.ptrt_destroy(h)
+assert threads() == 0
+""")
