@@ -55,11 +55,19 @@ inline int tile_core(int n, int most)
 // lattices and batches (64^2 ... 4096^2, FP32 and FP64): the fastest pass at
 // twelve, within 6 % (700^2) and 2 % of it at the others. The earlier passes
 // take about 2 us a launch and run at 113 (FP32), 64 (FP64) and 180 (16
-// bits) nodes a ns over rows padded to whole strips; they stay faster on
-// lattices of one or two rows, where a tile is mostly halo (600000 x 1 FP32
-// 6.2 us a step against 18.5), and for stochastic rounding on large
-// lattices, whose nine rounded stores double the issue time (2048^2 FP16 23
-// us against 38).
+// bits) nodes a ns over rows padded to whole strips. For stochastic rounding
+// on large lattices they stay the faster ones: its nine rounded stores double
+// the issue time (2048^2 FP16 23 us against 38).
+//
+// Lattices of few rows: a tile is mostly halo, and both estimates are off by
+// up to a quarter, so that long ones take tile passes only if these are
+// estimated faster by more than that (earlier -> tile passes, us a step:
+// 10000 x 1 FP32 2.08 -> 1.01, 10000 x 3 FP64 3.01 -> 1.40, 70000 x 4 FP32
+// 1.7 times faster, 1000000 x 8 FP32 2.0 times; but 100000 x 2 FP32 3.19 ->
+// 4.07, 100000 x 3 FP64 5.65 -> 7.81, 1000000 x 6 FP16 34.0 -> 46.9, 1000
+// lattices of 200 x 4 and 5 FP64 14.9 -> 18.2). In 16 bits a batch's earlier
+// pass is slower and the tile passes gain there (13.1 -> 10.7), so that only
+// long rows count.
 inline TilePlan choose_tile_plan(int storage, const std::vector<std::pair<int, int>> &sizes)
 {
     const size_t elem = storage_bytes(storage);
@@ -78,8 +86,18 @@ inline TilePlan choose_tile_plan(int storage, const std::vector<std::pair<int, i
         nodes += (double)n.first * n.second;
         padded += (double)((n.first + strip - 1) / strip * strip) * n.second;
     }
+    double thin = 0.0, columns = 0.0; // of the lattices of few rows
+    int rows = 0;
+    for (const auto &n : sizes) {
+        rows = std::max(rows, n.second);
+        if (n.second >= (half ? 12 : 6) || (half && n.first < 50000)) continue;
+        thin += (double)n.first * n.second;
+        columns += n.first;
+    }
+    const bool few_rows =
+        columns > (half && rows > 1 ? 99999.0 : 50000.0) && thin > (f64 ? 0.5 : 0.75) * nodes;
     TilePlan best;
-    double best_cost = 2.0 + padded / earlier_rate;
+    double best_cost = (2.0 + padded / earlier_rate) * (few_rows ? (f64 ? 0.75 : 0.8) : 1.0);
     for (int shape = 0; shape < TILE_SHAPES; ++shape) {
         with_tile_shape(shape, [&](auto sh) {
             using SH = decltype(sh);

@@ -181,3 +181,44 @@ assert threads() == most
 L.ptrt_destroy(h)
 assert threads() == 0
 """)
+
+
+def test_few_rows_keep_the_earlier_passes(run):
+    """Long lattices of few rows, and batches of them, whose tiles would be
+    mostly halo take the passes of one and two steps; short ones, those of
+    more rows and 16-bit batches take tile passes."""
+    run("""
+def kind(nx, ny, storage):
+    h = create(D2Q9, nx, ny, 1, storage)
+    init(h)
+    k = set(kernels(h, 10))
+    ok(L.ptrt_destroy(h), h)
+    assert len(k) == 1, k
+    return k.pop()
+
+for storage, few, earlier in ((F32, 6, "k_step2_2d"), (F64, 6, "k_step2_2d"), (F16, 12, "k_step")):
+    for nx in (100000, 1000000):
+        for ny in (1, 2, 3):
+            assert kind(nx, ny, storage) == earlier, (nx, ny, storage)
+    assert kind(1000000, few - 2, storage) == earlier
+    for nx, ny in ((100, 1), (10000, 1), (10000, 3), (1000000, 16), (7, 200000), (509, 381)):
+        assert kind(nx, ny, storage) == "k_tile_2d", (nx, ny, storage)
+assert kind(70000, 4, F32) == kind(1000000, 8, F32) == "k_tile_2d"
+
+def batch_kind(sizes, storage):
+    rc, b = batch(sizes, storage)
+    assert rc == 0
+    R.rec_reset()
+    assert L.ptrt_batch_step(b, 10) == 0
+    k = {l[0] for l in launches()}
+    L.ptrt_batch_destroy(b)
+    assert len(k) == 1, k
+    return k.pop()
+
+thin = [(200, 4), (210, 5)] * 500
+assert batch_kind(thin, F64) == batch_kind(thin, F32) == "k_batch_step2"
+assert batch_kind(thin, F16) == "k_batch_tile"
+for storage in (F64, F32, F16):
+    assert batch_kind(thin[:20], storage) == "k_batch_tile"
+    assert batch_kind(thin[:50] + [(300, 200)] * 20, storage) == "k_batch_tile"
+""")
