@@ -150,17 +150,22 @@ inline std::vector<uint8_t> near_solid_rows(const uint8_t *mask, int nx, int ny,
 // Tiled layout of a lattice (see kernels.hpp): rows padded to a pitch of a
 // whole number of 128-byte lines (a wave's row segment then starts on a
 // line boundary, so no line is written partly by two waves), rows per tile
-// chosen so one direction chunk of a tile is about 8 KB.  Returns the
-// element count of a population buffer and fills g.
-inline long long make_layout(int Q, int nx, int ny, int nz, size_t elem, Geom &g)
+// chosen so one direction chunk of a tile is about 8 KB.  whole_planes (3D):
+// at most so many that a plane is a whole number of tiles, and a node's
+// offset splits into a z part and an (x, y) part; one row for odd ny.  Only
+// for handles whose passes need it: one-step kernels are up to 8 % slower on
+// such short tiles where rows are a power of two long (us a step: D3Q19
+// 250 x 251 x 250 FP32 with Scheme I 429 -> 458, D3Q27 512 x 511 x 200 FP64
+// 3889 -> 4183, FP16 945 -> 1009; 300 x 301 x 300 and 200 x 151 x 120 within
+// 2 % except FP16 633 -> 610).  Returns the element count of a population
+// buffer and fills g.
+inline long long make_layout(int Q, int nx, int ny, int nz, size_t elem, Geom &g, bool whole_planes = false)
 {
     const long long line = (long long)(128 / elem);
     const int pitch = (int)(((long long)nx + line - 1) / line * line);
     int lr = 0;
     while (((long long)pitch << (lr + 1)) * (long long)elem <= 8192) ++lr;
-    // 3D: a plane is a whole number of tiles, so that a node's offset splits
-    // into a z part and an (x, y) part
-    while (Q > 9 && ny % (1 << lr) != 0) --lr;
+    while (whole_planes && ny % (1 << lr) != 0) --lr;
     g.nx = nx;
     g.ny = ny;
     g.nz = nz;

@@ -220,10 +220,47 @@ int plan_tiles(ptrt_ctx *c)
     return PTRT_OK;
 }
 
+// The layout of the populations: planes of whole tiles where the passes that
+// the handle is set up for need them, the march (march3d.hpp) and, in FP32,
+// the source offsets of k_step2, with (lists) or without solids.  A model or
+// forcing chosen later runs on the same layout, in the passes that it allows.
+void choose_layout(ptrt_ctx *c, bool lists)
+{
+    const size_t elem = storage_bytes(c->storage);
+    bool whole = false;
+    if (c->lattice == PTRT_D3Q19 && c->forcing == FORCE_II && c->model != MODEL_PTRT_EXACT) {
+        const bool offsets = c->storage == PTRT_F32 && c->nx % Step2Shape<D3Q19, float>::BX == 0 &&
+                             c->ny >= Step2Shape<D3Q19, float>::BY;
+        Geom g{};
+        make_layout(c->Q, c->nx, c->ny, c->nz, elem, g, true);
+        if (c->has_mask)
+            whole = c->model == MODEL_PTRT && (lists ? offsets : march_lattice(g, c->storage, true));
+        else
+            whole = offsets || (c->model == MODEL_PTRT && march_lattice(g, c->storage, false));
+    }
+    c->elems = make_layout(c->Q, c->nx, c->ny, c->nz, elem, c->geo, whole);
+}
+
 int allocate_device(ptrt_ctx *c)
 {
     const size_t elem = storage_bytes(c->storage);
-    c->elems = make_layout(c->Q, c->nx, c->ny, c->nz, elem, c->geo);
+    // D3Q19 with solids: the column chunks of the two-step pass, mask-free
+    // and masked (none when the pass does not apply)
+    std::vector<int4> plain3, special3;
+    if (c->has_mask) c->h_near = near_solid_rows(c->h_mask.data(), c->nx, c->ny, c->nz);
+    if (c->lattice == PTRT_D3Q19 && c->has_mask) {
+        make_layout(c->Q, c->nx, c->ny, c->nz, elem, c->geo);
+        bool ok = false;
+        if (c->storage == PTRT_F32)
+            ok = step2_3d_task_lists<D3Q19, float>(c->geo, c->h_near.data(), plain3, special3);
+        else if (c->storage == PTRT_F64)
+            ok = step2_3d_task_lists<D3Q19, double>(c->geo, c->h_near.data(), plain3, special3);
+        if (!ok) {
+            plain3.clear();
+            special3.clear();
+        }
+    }
+    choose_layout(c, !plain3.empty() || !special3.empty());
     const size_t bytes = (size_t)c->elems * elem;
     // Row workgroups covering 1 KB of each direction's row (measured best on
     // MI355X for every storage type); non-temporal stores once the two
@@ -243,26 +280,15 @@ int allocate_device(ptrt_ctx *c)
     if (c->has_mask) {
         HIPCHK(c, hipMalloc(&c->d_mask, (size_t)c->N));
         HIPCHK(c, hipMemcpy(c->d_mask, c->h_mask.data(), (size_t)c->N, hipMemcpyHostToDevice));
-        c->h_near = near_solid_rows(c->h_mask.data(), c->nx, c->ny, c->nz);
         HIPCHK(c, hipMalloc(&c->d_near, c->h_near.size()));
         HIPCHK(c, hipMemcpy(c->d_near, c->h_near.data(), c->h_near.size(), hipMemcpyHostToDevice));
     }
-    if (c->lattice == PTRT_D3Q19 && c->has_mask) {
-        // the 3D two-step pass with solids: mask-free and masked column
-        // chunks (none when the pass does not apply)
-        std::vector<int4> plain, special;
-        bool ok = false;
-        if (c->storage == PTRT_F32)
-            ok = step2_3d_task_lists<D3Q19, float>(c->geo, c->h_near.data(), plain, special);
-        else if (c->storage == PTRT_F64)
-            ok = step2_3d_task_lists<D3Q19, double>(c->geo, c->h_near.data(), plain, special);
-        if (ok && (!plain.empty() || !special.empty())) {
-            c->n_plain = (int)plain.size();
-            c->n_special = (int)special.size();
-            plain.insert(plain.end(), special.begin(), special.end());
-            HIPCHK(c, hipMalloc(&c->d_tasks, sizeof(int4) * plain.size()));
-            HIPCHK(c, hipMemcpy(c->d_tasks, plain.data(), sizeof(int4) * plain.size(), hipMemcpyHostToDevice));
-        }
+    if (!plain3.empty() || !special3.empty()) {
+        c->n_plain = (int)plain3.size();
+        c->n_special = (int)special3.size();
+        plain3.insert(plain3.end(), special3.begin(), special3.end());
+        HIPCHK(c, hipMalloc(&c->d_tasks, sizeof(int4) * plain3.size()));
+        HIPCHK(c, hipMemcpy(c->d_tasks, plain3.data(), sizeof(int4) * plain3.size(), hipMemcpyHostToDevice));
     }
     if (c->lattice == PTRT_D2Q9 && (c->has_mask || c->open)) {
         // the two-step kernel's tasks {0, x0, ys, ye}: strips of BX columns

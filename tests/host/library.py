@@ -9,7 +9,7 @@ R = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
 L = C.CDLL(sys.argv[2])
 R.rec_name.restype = C.c_char_p
 R.rec_limit_host.argtypes = [C.c_size_t]
-for name in ("rec_host_now", "rec_host_most"):
+for name in ("rec_host_now", "rec_host_most", "rec_device_size"):
     getattr(R, name).restype = C.c_size_t
 L.ptrt_last_error.restype = L.ptrt_batch_last_error.restype = C.c_char_p
 

@@ -37,7 +37,7 @@ int g_fail_device = 0, g_fail_host = 0; // the n-th allocation from now on fails
 int g_last_error = 0;
 size_t g_host_most = 0, g_host_now = 0;
 size_t g_host_limit = ~(size_t)0; // larger pinned allocations fail
-int g_device_allocs = 0;
+std::vector<size_t> g_device_sizes; // asked for since the last reset
 thread_local struct {
     Dim3 grid, block;
     size_t shared;
@@ -75,7 +75,7 @@ void rec_reset()
 {
     std::lock_guard<std::mutex> lock(g_mutex);
     g_log.clear();
-    g_device_allocs = 0;
+    g_device_sizes.clear();
 }
 int rec_launches() { return (int)g_log.size(); }
 const char *rec_name(int k) { return g_log[k].name.c_str(); }
@@ -90,7 +90,8 @@ int rec_pointer(int k, int arg) { return g_log[k].pointers[arg]; }
 void rec_fail_device(int n) { g_fail_device = n; }
 void rec_fail_host(int n) { g_fail_host = n; }
 void rec_limit_host(size_t bytes) { g_host_limit = bytes; }
-int rec_device_allocations() { return g_device_allocs; }
+int rec_device_allocations() { return (int)g_device_sizes.size(); }
+size_t rec_device_size(int k) { return g_device_sizes[k]; }
 size_t rec_host_now() { return g_host_now; }
 size_t rec_host_most() { return g_host_most; }
 int rec_blocks() { return (int)g_blocks.size(); }
@@ -150,7 +151,7 @@ int hipMalloc(void **p, size_t bytes)
 {
     std::lock_guard<std::mutex> lock(g_mutex);
     *p = nullptr;
-    ++g_device_allocs;
+    g_device_sizes.push_back(bytes);
     if (g_fail_device > 0 && --g_fail_device == 0) return g_last_error = OUT_OF_MEMORY;
     return allocate(p, bytes);
 }

@@ -222,3 +222,59 @@ for storage in (F64, F32, F16):
     assert batch_kind(thin[:20], storage) == "k_batch_tile"
     assert batch_kind(thin[:50] + [(300, 200)] * 20, storage) == "k_batch_tile"
 """)
+
+
+def test_layout_of_whole_planes_only_for_passes_that_need_it(run):
+    """Odd ny: rows share tiles (the buffer holds a multiple of the tile's
+    rows) in every kernel of one step per pass, and have one row a tile where
+    the march or k_step2's source offsets run."""
+    run("""
+SCHEME2, SCHEME2_G, GUO = 0, 1, 2
+PTRT, RLB, TRT, EXACT = 0, 1, 2, 3
+
+def rows(lattice, nx, ny, nz, storage, mask=None, forcing=SCHEME2, model=PTRT):
+    h = create(lattice, nx, ny, nz, storage, mask)
+    ok(L.ptrt_set_model(h, model), h)
+    ok(L.ptrt_set_forcing(h, forcing), h)
+    R.rec_reset()
+    init(h)
+    elem = {F64: 8, F32: 4}.get(storage, 2)
+    line = 128 // elem
+    pitch = (nx + line - 1) // line * line
+    n, q = R.rec_device_size(0), {D3Q19: 19, D3Q27: 27}[lattice]
+    ok(L.ptrt_destroy(h), h)
+    assert n % (q * pitch * elem) == 0
+    return n // (q * pitch * elem)
+
+def solid(nx, ny, nz):
+    return bytes([1]) + bytes(nx * ny * nz - 1)
+
+S = (60, 61, 61)
+whole = 61 * 61
+for storage in (F32, F64):
+    assert rows(D3Q19, *S, storage) == whole
+    assert rows(D3Q19, *S, storage, solid(*S)) == whole          # march with solids
+    for option in ({"forcing": GUO}, {"forcing": SCHEME2_G}, {"model": RLB}, {"model": TRT}, {"model": EXACT}):
+        assert rows(D3Q19, *S, storage, **option) > whole, option
+    assert rows(D3Q27, *S, storage) > whole
+for storage in (F16, BF16_SR):
+    assert rows(D3Q19, *S, storage) > whole and rows(D3Q27, *S, storage) > whole
+T = (128, 99, 99)                       # k_step2: source offsets in FP32 only
+assert rows(D3Q19, *T, F32) == rows(D3Q19, *T, F32, model=TRT) == 99 * 99
+assert rows(D3Q19, *T, F64) > 99 * 99
+U = (64, 99, 99)                        # FP32 with solids, strips of 32 columns: one step per pass
+assert rows(D3Q19, *U, F32, solid(*U)) > 99 * 99
+# a forcing chosen after the first init: the passes that the layout allows
+h = create(D3Q19, *S, F64)
+ok(L.ptrt_set_forcing(h, GUO), h)
+init(h)
+ok(L.ptrt_set_forcing(h, SCHEME2), h)
+assert set(kernels(h, 8)) == {"k_step"}
+h = create(D3Q19, *S, F64)
+init(h)
+assert set(kernels(h, 8)) == {"k_march3d"}
+ok(L.ptrt_set_forcing(h, GUO), h)
+assert set(kernels(h, 8)) == {"k_step"}
+ok(L.ptrt_set_forcing(h, SCHEME2), h)
+assert set(kernels(h, 8)) == {"k_march3d"}
+""")
