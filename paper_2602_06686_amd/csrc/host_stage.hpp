@@ -60,11 +60,20 @@ public:
         for (int k = 0; k < kept_; ++k) (void)hipHostFree(keep_[k].ptr);
     }
 
-    // A transfer of this many bytes begins.
-    void announce(long long bytes)
+    // A transfer of this many bytes begins: the pinned bytes for its ring, about
+    // a twentieth of all transfers so far, from 4 to 64 MB.  Pinned memory that
+    // is new costs the host 380 us a megabyte in page faults, so that large
+    // rings have to be earned: a handle on 64^3 nodes, made, read once and
+    // freed, takes 1.1 ms with pageable copies, 2.7 with a ring of 16 MB and
+    // 0.9 with 4.
+    static constexpr long long LEAST = 4 << 20, MOST = 64 << 20;
+    long long ring_bytes(long long bytes)
     {
         std::lock_guard<std::mutex> lock(mutex_);
         moved_ += bytes;
+        long long r = LEAST;
+        while (r < MOST && r <= moved_ / 32) r *= 2;
+        return r;
     }
 
     // f(i) for i = 0 ... n - 1, on the caller and the pool's threads.
@@ -158,17 +167,19 @@ private:
     HostPool() = default;
 
     // Whether there are threads for n pieces: up to n - 1, one per megabyte of
-    // the transfers so far and none below 8 MB, so that a handle that is made,
+    // the transfers so far and none below 24 MB, so that a handle that is made,
     // read once and freed does not pay for threads that it hardly uses.
     // Starting and joining one takes 67 us, fifteen 285 us, as long as the
-    // caller alone takes for 1 and 4 MB (32^3 FP32, made, ten steps, read,
-    // freed: 388 us with pageable copies, 739 with fifteen threads at once).
-    // Fewer, or none, where the system refuses.
+    // caller alone takes for 1 and 4 MB (made, ten steps, read, freed, us:
+    // 32^3 FP32 388 with pageable copies, 739 with fifteen threads at once;
+    // 64^3 made, one step, read, freed 1050 with threads from 8 MB on, 900 from
+    // 24).  Fewer, or none, where the system refuses.
     bool ready(int n)
     {
         std::lock_guard<std::mutex> lock(mutex_);
         const long long mb = moved_ >> 20;
-        const int want = mb < 8 ? 0 : (int)std::min<long long>(std::min(most_, n - 1), mb);
+        if (mb >= 24 && most_ < 0) most_ = std::min(MAX_THREADS, (int)std::thread::hardware_concurrency() - 1);
+        const int want = mb < 24 ? 0 : (int)std::min<long long>(std::min(most_, n - 1), mb);
         try {
             while (!refused_ && threads_ < want) {
                 thread_[threads_] = std::thread([this] { serve(); });
@@ -199,7 +210,7 @@ private:
     }
 
     const pid_t pid_ = getpid();
-    const int most_ = std::min(MAX_THREADS, (int)std::thread::hardware_concurrency() - 1);
+    int most_ = -1; // threads at most; not looked up yet
     std::mutex mutex_;
     std::condition_variable work_, idle_;
     Job *jobs_ = nullptr;
@@ -215,20 +226,20 @@ private:
 class StageRing {
 public:
     static constexpr int RING = 4;
-    // per_node: bytes of one node.  Chunks of at most 16 MB, a quarter of a
-    // smaller transfer (not below 2 MB), so that they overlap.  The host's
-    // share, page faults above all, is the longer one: 256^3 moments in a
-    // sampling loop 17.8 ms with 8 MB and 8 threads, 14.6 with 16 and 16.
+    // per_node: bytes of one node.  Up to 2 MB in one chunk; more in a ring of
+    // the pool's choice, of two chunks at its least size and four beyond, that
+    // overlap.  The host's share, page faults of the caller's fresh arrays
+    // above all, is the longer one, and larger chunks keep more threads busy:
+    // 256^3 moments in a sampling loop 17.8 ms with chunks of 8 MB and 8
+    // threads, 14.6 with 16 and 16.
     StageRing(const std::shared_ptr<HostPool> &pool, long long nodes, size_t per_node, hipStream_t stream)
         : pool_(pool), nodes_(nodes), per_node_(per_node), stream_(stream)
     {
-        const double total = (double)nodes * (double)per_node;
-        const double chunk = std::max(2048.0 * 1024, total / RING);
-        // never a node over the 16 MB: take() rounds up to a power of two
-        const long long most = std::max(1LL, (long long)((16u << 20) / per_node));
-        step_ = std::min({nodes, most, (long long)(chunk / (double)per_node) + 1});
+        const long long total = nodes * (long long)per_node, ring = pool->ring_bytes(total);
+        const int most = ring == HostPool::LEAST ? 2 : RING;
+        step_ = total <= HostPool::LEAST / 2 ? nodes : std::max(1LL, std::min(ring, total) / most / (long long)per_node);
         chunks_ = (nodes + step_ - 1) / step_;
-        slots_ = (int)std::min<long long>(RING, chunks_);
+        slots_ = (int)std::min<long long>(most, chunks_);
     }
     ~StageRing()
     {
@@ -281,7 +292,6 @@ private:
     {
         stage_ = pool_->take((size_t)step_ * per_node_ * (size_t)slots_);
         if (!stage_.ptr) return hipErrorOutOfMemory;
-        pool_->announce(nodes_ * (long long)per_node_);
         for (int k = 0; k < slots_ && chunks_ > 1; ++k) {
             const hipError_t e = hipEventCreateWithFlags(&event_[k], hipEventDisableTiming);
             if (e != hipSuccess) return e;

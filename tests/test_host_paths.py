@@ -154,32 +154,43 @@ L.ptrt_destroy(h)
 """)
 
 
-def test_threads_only_for_what_is_moved(run):
-    """A small handle that is read a few times starts no thread; one that is
-    read on and on, or a large one, as many as its pieces keep busy."""
+def test_threads_and_pinned_memory_for_what_is_moved(run):
+    """A small handle that is read a few times starts no thread and pins no
+    more than it moves at once, at most 4 MB; handles that move much, as many
+    threads as their pieces keep busy and at most 64 MB a ring."""
     run("""
 import os
 threads = lambda: len(os.listdir("/proc/self/task")) - 1
 most = min(15, len(os.sched_getaffinity(0)) - 1)
-n = 32 * 32 * 32
-rho, u = (C.c_double * n)(), (C.c_double * (3 * n))()
+
+def arrays(n):
+    return (C.c_double * n)(), (C.c_double * (3 * n))()
+
+rho, u = arrays(32 ** 3)
 h = create(D3Q19, 32, 32, 32)
 ok(L.ptrt_init_equilibrium(h, rho, u), h)       # 1 MB, four pieces
 for _ in range(5):
     ok(L.ptrt_moments(h, rho, u), h)
-assert threads() == 0, threads()
-for _ in range(5):
+assert threads() == 0 and R.rec_host_most() == 1 << 20
+for _ in range(30):
     ok(L.ptrt_moments(h, rho, u), h)
 assert threads() == min(3, most), threads()
 L.ptrt_destroy(h)
-assert threads() == 0
-n = 128 * 128 * 128
-rho, u = (C.c_double * n)(), (C.c_double * (3 * n))()
-h = create(D3Q19, 128, 128, 128)
-ok(L.ptrt_init_equilibrium(h, rho, u), h)
-assert threads() == most
+assert threads() == 0 and R.rec_host_now() == 0
+rho, u = arrays(64 ** 3)
+h = create(D3Q19, 64, 64, 64)
+ok(L.ptrt_init_equilibrium(h, rho, u), h)       # 8 MB
+ok(L.ptrt_moments(h, rho, u), h)
+assert R.rec_host_most() == 4 << 20 and threads() == 0
 L.ptrt_destroy(h)
-assert threads() == 0
+rho, u = arrays(128 ** 3)
+h = create(D3Q19, 128, 128, 128)
+for _ in range(40):                             # 2.7 GB
+    ok(L.ptrt_moments(h, rho, u), h) if _ else ok(L.ptrt_init_equilibrium(h, rho, u), h)
+assert threads() == most
+assert 64 << 20 <= R.rec_host_now() <= 128 << 20 and R.rec_host_most() <= 192 << 20
+L.ptrt_destroy(h)
+assert threads() == 0 and R.rec_host_now() == 0
 """)
 
 
