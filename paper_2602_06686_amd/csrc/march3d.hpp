@@ -7,29 +7,36 @@
 // (lanes 0 ... cols + 1 are columns x0 - 1 ... x0 + cols): each of its BY + 2
 // waves computes one row of first steps a plane, and BY of them the second
 // step of their own row, with no separate halo task and one set of pulls
-// per wave in flight.  FP32 100 registers, two workgroups per CU; FP64 190,
-// one.  Bound by instruction issue (14 collisions for six rows of two steps,
-// idle lanes past cols) and, on small lattices, by the chain of a chunk's
-// planes, about 4 us each with two workgroups on a CU.  The strips start
+// per wave in flight.  FP32 100 registers (with solids 128, 5 of them
+// spilled), two workgroups per CU; FP64 190, one.  Bound by instruction issue
+// (14 collisions for six rows of two steps, idle lanes past cols) and, on
+// small lattices, by the chain of a chunk's planes, about 4 us each with two
+// workgroups on a CU.  The strips start
 // anywhere in a 128-byte line: plain stores, whose parts meet in L2 (the
 // non-temporal ones of k_step2 measured up to 13 % slower here).
 //
 // SOLID: link flags per node, formed once per lattice, are loaded one plane
-// before the pulls that depend on them; a row of 64 nodes without any takes
-// the plain code, so walls and blocks cost the rows at them only.  What
-// bounces back in the second step is the node's own first-step value, in LDS
-// for e_z >= 0 and, for the e_z = -1 class that LDS keeps for one plane, in
-// the wave's registers.
+// before the pulls that depend on them; a row of 64 lanes without any takes
+// the plain code, so walls and blocks cost the rows at them only.  For the
+// second step a node puts what bounces back to it into the LDS slot of the
+// solid that it would be read from (a solid writes no slots, and each slot
+// has one reader): for e_z >= 0 in its own first step, for e_z = -1, whose
+// source's plane comes next, an iteration later from its own slot.  The
+// second step then reads as without solids.  Registers of the nodes'
+// e_z = -1 values over three planes instead, and a second step with a branch
+// on the flags, took 214 registers in FP64 and spilled 21 in FP32 (us a
+// step, one step per pass / that / this, with walls: FP32 160 x 100 x 102
+// 38.6 / 42.4 / 34.5, FP64 128 x 100 x 102 69.4 / 54.6 / 53.0).
 #pragma once
 
 #include "step2.hpp"
 
 namespace ptrt {
 
-// Columns of a strip: near-equal strips of at most 62.
-inline int march_cols(int nx)
+// Columns of a strip: near-equal strips of at most W - 2 (rows of W lanes).
+inline int march_cols(int nx, int W = 64)
 {
-    const int strips = (nx + 61) / 62;
+    const int strips = (nx + W - 3) / (W - 2);
     return (nx + strips - 1) / strips;
 }
 
@@ -54,9 +61,13 @@ k_link_flags(const uint8_t *__restrict__ mask, Geom g, NodeRange r, unsigned *__
     flags[r.node] = f;
 }
 
-template <class S, int BY_>
+// Rows of W lanes: a wave's whole row, or two rows of 32 lanes a wave for
+// lattices that fill so few of 64 (24 to 40 columns, and 63 to 80, whose
+// strips of 64 lanes would be half empty).
+template <class S, int BY_, int W_ = 64>
 struct MarchShape {
-    static constexpr int W = 64, BY = BY_, AY = BY + 2, AP = AY * W;
+    static constexpr int W = W_, BY = BY_, AY = BY + 2, AP = AY * W;
+    static_assert(W == 64 || W == 32, "rows of a wave or half a wave");
     using K = Step2Classes<D3Q19, 2>;
     static constexpr int PAD = W; // sources of the garbage lanes 0 and 63
     static constexpr int elems = K::planes * AP + 2 * PAD;
@@ -65,7 +76,7 @@ struct MarchShape {
 };
 
 template <class S, class SH, bool SOLID>
-__global__ void __launch_bounds__((64 * SH::AY))
+__global__ void __launch_bounds__(SH::AP)
 __attribute__((amdgpu_waves_per_eu(SH::template waves_per_simd<S>, SH::template waves_per_simd<S>)))
 k_march3d(const S *__restrict__ src, S *__restrict__ dst, const unsigned *__restrict__ flags, Geom g,
           Coef<D3Q19, typename Codec<S>::compute> r, int zc, int cols)
@@ -79,8 +90,10 @@ k_march3d(const S *__restrict__ src, S *__restrict__ dst, const unsigned *__rest
     int bx, by, bz;
     xcd_block(bx, by, bz);
     const int x0 = bx * cols, y0 = by * BY, zs = bz * zc, ze = min(zs + zc, g.nz);
-    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int lane = (int)(threadIdx.x & 63);
+    // row of the workgroup and lane of the row
+    int w = (int)threadIdx.x / W;
+    if constexpr (W == 64) w = __builtin_amdgcn_readfirstlane(w);
+    const int lane = (int)threadIdx.x & (W - 1);
     auto mod = [](int v, int n) {
         v %= n;
         return v < 0 ? v + n : v;
@@ -90,7 +103,7 @@ k_march3d(const S *__restrict__ src, S *__restrict__ dst, const unsigned *__rest
     // column: their values are not used)
     const int x = mod(x0 - 1 + min(lane, cols + 1), g.nx), y = mod(y0 - 1 + w, g.ny);
     const bool b_lane = lane >= 1 && lane <= cols && x0 - 1 + lane < g.nx;
-    const bool b_wave = w >= 1 && w <= BY;
+    const bool b_row = w >= 1 && w <= BY;
     // byte offsets of the lane's sources inside a plane of the layout
     const long long zstride = (long long)(g.ny >> g.lr) * g.tile * (long long)sizeof(S);
     unsigned off[L::Q];
@@ -131,66 +144,78 @@ k_march3d(const S *__restrict__ src, S *__restrict__ dst, const unsigned *__rest
         return (K::region(i_cls) + slot * K::count(i_cls) + i_idx) * AP + a;
     };
     const int own = w * W + lane;
-    // first step of plane `it`; down: with SOLID the e_z = -1 values, which
-    // LDS keeps for one plane only and a node above a solid takes back in its
-    // own second step, one iteration later
-    constexpr int ND = SOLID ? K::count(0) : 1;
-    auto first = [&](int it, const S (&raw)[L::Q], S (&down)[ND]) __attribute__((always_inline)) {
+    // first step of plane `it`; f, fp: link flags of this plane and of the one
+    // below
+    auto first = [&](int it, const S (&raw)[L::Q], unsigned f, unsigned fp) __attribute__((always_inline)) {
         C h[L::Q];
         static_for<L::Q>([&](auto ic) { h[decltype(ic)::value] = Codec<S>::load(&raw[decltype(ic)::value]); });
         C rho, ux, uy, uz;
         collide_pass<L, S>(h, r, rho, ux, uy, uz);
+        if (!(SOLID && (f & 1u)))
+            static_for<L::Q>([&](auto ic) {
+                constexpr int i = decltype(ic)::value;
+                constexpr int c = K::cls(i);
+                Codec<S>::template store<false>(&lds[slot_of(c, K::index(i), it % K::slots(c), own)], h[i]);
+            });
+        if constexpr (SOLID) {
+            const bool core = b_row && b_lane && it > 0;
+            if (__any(core && (f | fp) > 1u)) {
+                if (!core) return;
+                static_for<L::Q>([&](auto ic) {
+                    constexpr int i = decltype(ic)::value;
+                    constexpr int c = K::cls(i), o = L::opp(i), co = K::cls(o);
+                    const int to = own - (L::ey(i) * W + L::ex(i));
+                    if constexpr (i != 0 && c != 0) {
+                        // from the source's plane, this one or the one below
+                        if ((f >> i) & 1u && !(f & 1u))
+                            Codec<S>::template store<false>(
+                                &lds[slot_of(c, K::index(i), (it + 1 - c) % K::slots(c), to)], h[o]);
+                    } else if constexpr (c == 0) {
+                        // of the node below this one, whose source is in this plane
+                        if ((fp >> i) & 1u && !(fp & 1u))
+                            lds[slot_of(c, K::index(i), it % K::slots(c), to)] =
+                                lds[slot_of(co, K::index(o), (it - 1) % K::slots(co), own)];
+                    }
+                });
+            }
+        }
+    };
+    // second step of plane k - 1, iteration it (first steps up to plane k); f:
+    // link flags of plane k - 1
+    auto second = [&](int k, int it, unsigned f) __attribute__((always_inline)) {
+        C h[L::Q];
         static_for<L::Q>([&](auto ic) {
             constexpr int i = decltype(ic)::value;
             constexpr int c = K::cls(i);
-            S v;
-            Codec<S>::template store<false>(&v, h[i]);
-            lds[slot_of(c, K::index(i), it % K::slots(c), own)] = v;
-            if constexpr (SOLID && c == 0) down[K::index(i)] = v;
+            h[i] = Codec<S>::load(&lds[slot_of(c, K::index(i), (it - c) % K::slots(c),
+                                               own - (L::ey(i) * W + L::ex(i)))]);
         });
-    };
-    // second step of plane k - 1, iteration it (first steps up to plane k);
-    // f, down: flags and e_z = -1 values of plane k - 1
-    auto second = [&](int k, int it, unsigned f, const S (&down)[ND]) __attribute__((always_inline)) {
-        auto row = [&](auto bc) __attribute__((always_inline)) {
-            constexpr bool BACK = decltype(bc)::value;
-            C h[L::Q];
-            static_for<L::Q>([&](auto ic) {
-                constexpr int i = decltype(ic)::value;
-                constexpr int c = K::cls(i), o = L::opp(i), co = K::cls(o);
-                int a = slot_of(c, K::index(i), (it - c) % K::slots(c), own - (L::ey(i) * W + L::ex(i)));
-                if constexpr (BACK && i != 0 && co != 0)
-                    if ((f >> i) & 1u) a = slot_of(co, K::index(o), (it - 1) % K::slots(co), own);
-                h[i] = Codec<S>::load(&lds[a]);
-                if constexpr (BACK && i != 0 && co == 0)
-                    if ((f >> i) & 1u) h[i] = Codec<S>::load(&down[K::index(o)]);
-            });
-            C rho, ux, uy, uz;
-            collide_pass<L, S>(h, r, rho, ux, uy, uz);
-            if (!b_lane || (BACK && (f & 1u))) return;
-            char *db = reinterpret_cast<char *>(dst) + (long long)wrapz(k - 1) * zstride;
-            static_for<L::Q>([&](auto ic) {
-                constexpr int i = decltype(ic)::value;
-                Codec<S>::store(reinterpret_cast<S *>(db + (size_t)i * dir + off[0]), h[i]);
-            });
-        };
-        if (SOLID && __any(f != 0)) row(std::bool_constant<SOLID>{});
-        else row(std::false_type{});
+        C rho, ux, uy, uz;
+        collide_pass<L, S>(h, r, rho, ux, uy, uz);
+        if (!b_lane || (SOLID && (f & 1u))) return;
+        char *db = reinterpret_cast<char *>(dst) + (long long)wrapz(k - 1) * zstride;
+        static_for<L::Q>([&](auto ic) {
+            constexpr int i = decltype(ic)::value;
+            Codec<S>::store(reinterpret_cast<S *>(db + (size_t)i * dir + off[0]), h[i]);
+        });
     };
 
     // first steps of planes zs - 1, zs and zs + 1; then for k = zs + 1 ... ze
     // the second step of plane k - 1 and the first step of plane k + 1,
     // whose pulls were issued an iteration before (past the chunk the last
     // plane is loaded again)
-    S raw[L::Q], d0[ND], d1[ND], d2[ND]; // e_z = -1 values of planes k - 1, k, k + 1
+    S raw[L::Q];
     unsigned f0 = load_flags(zs - 1), f1 = load_flags(zs), f2 = load_flags(zs + 1),
              f3 = load_flags(min(zs + 2, ze));
     load(zs - 1, f0, raw);
-    first(0, raw, d0);
+    first(0, raw, f0, 0);
     load(zs, f1, raw);
-    first(1, raw, d0);
+    first(1, raw, f1, f0);
     load(zs + 1, f2, raw);
-    first(2, raw, d1);
+    // a value that bounces back from plane zs + 1 must not be met by one of
+    // plane zs - 1 or zs in the same slot
+    if constexpr (SOLID) lds_barrier();
+    first(2, raw, f2, f1);
     // f0 ... f3: flags of planes k - 1 ... k + 2
     f0 = f1;
     f1 = f2;
@@ -199,14 +224,10 @@ k_march3d(const S *__restrict__ src, S *__restrict__ dst, const unsigned *__rest
     f3 = load_flags(min(zs + 3, ze));
     for (int k = zs + 1, it = 2;; ++k, ++it) {
         lds_barrier();
-        if (b_wave) second(k, it, f0, d0);
+        if (b_row) second(k, it, f0);
         lds_barrier();
         if (k == ze) break;
-        first(it + 1, raw, d2);
-        for (int j = 0; j < ND; ++j) {
-            d0[j] = d1[j];
-            d1[j] = d2[j];
-        }
+        first(it + 1, raw, f2, f1);
         f0 = f1;
         f1 = f2;
         f2 = f3;

@@ -199,12 +199,17 @@ constexpr int MARCH_SOLID_MIN_STEPS = 8;
 // 300^3 FP32 970 -> 626, FP64 1584 -> 970) unless its rows are mostly idle
 // lanes: at least 24 columns, and in FP32 at least 42 once the lattice is
 // too large for the last-level cache to hide the others' loads (130^3, 44
-// columns, 67.4 -> 65.5).  With solids (walls or a block over 1/8 of each
-// axis; one step per pass before) FP64 gains throughout (128 x 96 x 96 63 ->
-// 54, 100 x 84 x 92 44 -> 30, 200^3 470 -> 319, 256^3 854 -> 609), FP32 with
-// rows mostly full below 6 million nodes (50 x 60 x 70 10.8 -> 9.6, 180 x
-// 160 x 170 156 -> 134; 128 x 96 x 96, 43 columns, 28.5 -> 32.3, 200^3 241
-// -> 284: its flags take the registers of eight waves per SIMD).
+// columns, 67.4 -> 65.5; 24 to 42 columns: 24 x 100 x 102 FP32 10.3 -> 10.0,
+// FP64 15.7 -> 15.2, 32 x 200 x 150 23.6 -> 19.8, 54.3 -> 47.6).  With solids
+// (walls or a block over 1/8 of each axis; one step per pass before) it is
+// faster with at least 24 columns in FP64 (24 x 100 x 102 17.4 -> 12.9, 128
+// x 96 x 96 62.9 -> 49.7, 200^3 471 -> 319, 256^3 854 -> 614; 32 columns
+// within 2 % either way), and in FP32 with rows mostly full and below 6
+// million nodes (50 x 100 x 102 17.9 -> 13.9, 100 x 84 x 92 23.8 -> 19.6,
+// 180 x 150 x 150 128 -> 103).  Small lattices, whose one step is a launch and
+// little more, and in FP32 four strips or more beyond 1.5 million nodes keep
+// one step per pass (FP32 60 x 40 x 40 6.0 -> 6.7, 100 x 40 x 40 7.5 -> 8.5,
+// 200 x 100 x 102 58.4 -> 62.0; FP64 64 x 40 x 40 8.1 -> 8.8).
 inline bool march_lattice(const Geom &g, int storage, bool solids)
 {
     if (storage != PTRT_F32 && storage != PTRT_F64) return false;
@@ -213,8 +218,11 @@ inline bool march_lattice(const Geom &g, int storage, bool solids)
     if (g.ny % (1 << g.lr) != 0 || (double)(g.ny >> g.lr) * (double)g.tile * (double)elem >= 4294967296.0)
         return false;
     const double nodes = (double)g.nx * g.ny * g.nz;
-    const int cols = march_cols(g.nx);
-    if (solids) return nodes >= 8e4 && (elem == 8 ? cols >= 24 : cols >= 48 && nodes <= 6e6);
+    const int cols = march_cols(g.nx), strips = (g.nx + cols - 1) / cols;
+    if (solids && elem == 8) return nodes >= (strips > 1 ? 1.6e5 : 1e5) && cols >= 24;
+    if (solids)
+        return nodes >= (strips > 1 ? 2e5 : 1e5) && nodes <= 6e6 &&
+               cols >= (strips > 3 && nodes > 1.5e6 ? 56 : 48);
     if (g.nx % Step2Shape<D3Q19, float>::BX == 0 && g.ny >= Step2Shape<D3Q19, float>::BY) return nodes < 8e5;
     return nodes >= 8e4 && cols >= (elem == 4 && nodes > 1.5e6 ? 42 : 24);
 }
@@ -226,21 +234,22 @@ inline bool march_applies(const StepLaunch &a)
 }
 
 // Planes per chunk: as step2_3d_zc, down to single planes (a small lattice
-// takes short chains over many workgroups).
+// takes short chains over many workgroups).  cost: rounds of resident
+// workgroups times the planes that each marches over.
 template <class S, class SH, bool SOLID>
-int march_zc(const Geom &g)
+int march_zc(const Geom &g, double *cost_out = nullptr)
 {
     static const int resident = [] {
         int per_cu = 0, dev = 0, cus = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &per_cu, reinterpret_cast<const void *>(&k_march3d<S, SH, SOLID>), 64 * SH::AY, 0) != hipSuccess ||
+                &per_cu, reinterpret_cast<const void *>(&k_march3d<S, SH, SOLID>), SH::AP, 0) != hipSuccess ||
             hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
             per_cu <= 0 || cus <= 0)
             return 256;
         return per_cu * cus;
     }();
-    const int cols = march_cols(g.nx);
+    const int cols = march_cols(g.nx, SH::W);
     const long long columns = (long long)((g.nx + cols - 1) / cols) * ((g.ny + SH::BY - 1) / SH::BY);
     int zc = g.nz;
     double best = -1.0;
@@ -254,6 +263,7 @@ int march_zc(const Geom &g)
         }
         if (wgs >= 16LL * resident) break;
     }
+    if (cost_out) *cost_out = best;
     return zc;
 }
 
@@ -267,12 +277,27 @@ void launch_march(const StepLaunch &a, double *pass_bytes)
     auto go = [&](auto sh, auto mc) {
         using SH = decltype(sh);
         constexpr bool SOLID = decltype(mc)::value;
-        const int cols = march_cols(a.g.nx), zc = march_zc<S, SH, SOLID>(a.g);
+        const int cols = march_cols(a.g.nx, SH::W), zc = march_zc<S, SH, SOLID>(a.g);
         const dim3 grid((a.g.nx + cols - 1) / cols, (a.g.ny + SH::BY - 1) / SH::BY, (a.g.nz + zc - 1) / zc);
-        hipLaunchKernelGGL((k_march3d<S, SH, SOLID>), grid, dim3(64 * SH::AY), 0, a.stream, (const S *)a.src,
+        hipLaunchKernelGGL((k_march3d<S, SH, SOLID>), grid, dim3(SH::AP), 0, a.stream, (const S *)a.src,
                            (S *)a.dst, a.link_flags, a.g, r, zc, cols);
     };
     if (a.has_mask) {
+        if constexpr (sizeof(S) == 8) {
+            // fourteen rows of 32 lanes, of the same threads and memory, where
+            // strips of 64 lanes are a third empty and those need fewer
+            // rounds or planes, or far fewer (us a step, one step per pass /
+            // 64 lanes / 32: 24 x 100 x 102 with a block 16.2 / 18.0 / 13.1,
+            // 64 x 60 x 61 with walls 13.4 / 16.2 / 12.5; 126 x 100 x 102 with
+            // walls, 42 columns, 69.7 / 55.1 / 62.4: more strips, more halo)
+            double wide = 0.0, narrow = 0.0;
+            march_zc<S, MarchShape<S, 6>, true>(a.g, &wide);
+            march_zc<S, MarchShape<S, 14, 32>, true>(a.g, &narrow);
+            if (narrow < (march_cols(a.g.nx) <= 40 ? 1.0 : 0.7) * wide) {
+                go(MarchShape<S, 14, 32>{}, std::true_type{});
+                return;
+            }
+        }
         go(MarchShape<S, 6>{}, std::true_type{});
         return;
     }

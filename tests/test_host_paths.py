@@ -289,3 +289,65 @@ assert set(kernels(h, 8)) == {"k_step"}
 ok(L.ptrt_set_forcing(h, SCHEME2), h)
 assert set(kernels(h, 8)) == {"k_march3d"}
 """)
+
+
+def test_march_with_solids_rows_of_32_lanes(run):
+    """FP64 with solids: rows of 32 lanes where strips of 64 have at most 40
+    columns and need more rounds, never in FP32 or without solids."""
+    run("""
+def shape(nx, ny, nz, storage, solids=True):
+    h = create(D3Q19, nx, ny, nz, storage, bytes([1]) + bytes(nx * ny * nz - 1) if solids else None)
+    init(h)
+    (l,) = set(step(h, 8))
+    ok(L.ptrt_destroy(h), h)
+    strips = {"64": 62, "32": 30}
+    if l[0] != "k_march3d":
+        return l[0]
+    args = l[1].split("<")[1].split(">")[0].split(", ")   # storage, rows, lanes
+    lanes, rows = int(args[2]), int(args[1])
+    assert l[3] == (lanes * (rows + 2), 1, 1)
+    n = -(-nx // (lanes - 2))
+    assert l[2][0] == -(-nx // -(-nx // n)) and l[2][1] == -(-ny // rows)
+    return lanes
+
+for nx in (24, 30, 64, 65, 80):
+    assert shape(nx, 100, 102, F64) == 32, nx
+    assert shape(nx, 100, 102, F64, False) == 64
+    assert shape(nx, 100, 102, F32) == "k_step"
+for nx in (48, 62, 96, 126, 128):  # 42 columns and more
+    assert shape(nx, 100, 102, F64) == 64, nx
+assert shape(50, 100, 102, F32) == 64
+""")
+
+
+@pytest.mark.parametrize("storage", ["F32", "F64"])
+def test_kernel_of_a_pair_of_steps_in_3d(run, storage):
+    """k_step2 from 800 000 nodes on where nx is a multiple of 64 (one launch
+    per round of resident workgroups), the march below; source offsets in
+    FP32, the general pulls for a handle first initialised with Scheme I."""
+    run(f"""
+def pair(nx, ny, nz, forcing=0):
+    h = create(D3Q19, nx, ny, nz, {storage})
+    ok(L.ptrt_set_forcing(h, forcing), h)
+    init(h)
+    ok(L.ptrt_set_forcing(h, 0), h)
+    out = step(h, 2)
+    ok(L.ptrt_destroy(h), h)
+    assert len({{l[0] for l in out}}) == 1
+    return out
+
+f32 = {storage} == F32
+for nx, ny, nz in ((128, 65, 99), (64, 101, 128), (64, 3130, 4), (128, 6255, 1), (128, 3133, 2), (128, 1370, 5),
+                   (192, 67, 66)):
+    out = pair(nx, ny, nz)
+    assert out[0][0] == "k_step2" and out[0][1].endswith("true" if f32 else "false"), out[0]
+    assert sum(l[2][1] for l in out) == -(-ny // 4)
+    ragged = pair(nx, ny, nz, 2)
+    assert ragged[0][0] == "k_step2"
+    if ny % 2:
+        assert ragged[0][1].endswith("false")
+assert len(pair(64, 3130, 4)) == 2                    # rows of workgroups in two rounds
+for nx, ny, nz in ((64, 64, 64), (128, 64, 64), (128, 60, 100), (192, 64, 64)):
+    assert pair(nx, ny, nz)[0][0] == "k_march3d"
+assert pair(64, 64, 64)[0][0] == pair(100, 84, 92)[0][0] == "k_march3d"
+""")
