@@ -673,31 +673,14 @@ int autotune2(ptrt_batch *b, hipEvent_t e0, hipEvent_t e1)
     return build_tasks2(b);
 }
 
-} // namespace
-
-extern "C" {
-
-int ptrt_batch_create(int count, const ptrt_instance_desc *desc, int storage, ptrt_batch **out)
+// The batch's tables and device memory; on failure it is freed and
+// g_batch_create_error holds the message.
+int fill_batch(ptrt_batch *b, int count, const ptrt_instance_desc *desc, int storage, ptrt_batch **out)
 {
-    if (!out || !desc || count <= 0) {
-        g_batch_create_error = "need count > 0 and non-NULL desc / out";
-        return PTRT_EINVAL;
-    }
-    *out = nullptr;
-    if (storage_bytes(storage) == 0) {
-        g_batch_create_error = "unknown storage type";
-        return PTRT_EINVAL;
-    }
-    ptrt_batch *b = new (std::nothrow) ptrt_batch();
-    if (!b) return PTRT_ENOMEM;
     b->count = count;
     b->storage = storage;
     b->pool = HostPool::shared();
-    if (!b->pool) {
-        delete b;
-        g_batch_create_error = "out of host memory";
-        return PTRT_ENOMEM;
-    }
+    if (!b->pool) throw std::bad_alloc();
     b->inst.resize(count);
     const size_t elem = storage_bytes(storage);
     std::vector<uint8_t> mask, near;
@@ -808,6 +791,32 @@ int ptrt_batch_create(int count, const ptrt_instance_desc *desc, int storage, pt
     }
     *out = b;
     return PTRT_OK;
+}
+
+} // namespace
+
+extern "C" {
+
+int ptrt_batch_create(int count, const ptrt_instance_desc *desc, int storage, ptrt_batch **out)
+{
+    if (!out || !desc || count <= 0) {
+        g_batch_create_error = "need count > 0 and non-NULL desc / out";
+        return PTRT_EINVAL;
+    }
+    *out = nullptr;
+    if (storage_bytes(storage) == 0) {
+        g_batch_create_error = "unknown storage type";
+        return PTRT_EINVAL;
+    }
+    ptrt_batch *b = new (std::nothrow) ptrt_batch();
+    if (!b) return PTRT_ENOMEM;
+    try {
+        return fill_batch(b, count, desc, storage, out);
+    } catch (const std::bad_alloc &) { // of the host's tables
+        ptrt_batch_destroy(b);
+        g_batch_create_error = "no host memory";
+        return PTRT_ENOMEM;
+    }
 }
 
 int ptrt_batch_set_stream(ptrt_batch *b, void *s)

@@ -174,8 +174,13 @@ int ensure_allocated(ptrt_ctx *c)
 {
     if (c->allocated) return PTRT_OK;
     c->pool = HostPool::shared();
-    if (!c->pool) return fail(c, PTRT_ENOMEM, "out of host memory");
-    const int rc = allocate_device(c);
+    if (!c->pool) return fail(c, PTRT_ENOMEM, "no host memory");
+    int rc;
+    try {
+        rc = allocate_device(c);
+    } catch (const std::bad_alloc &) { // of the host's tables
+        rc = fail(c, PTRT_ENOMEM, "no host memory");
+    }
     if (rc != PTRT_OK) {
         release_device(c);
         return rc;

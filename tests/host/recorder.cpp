@@ -10,6 +10,7 @@
 #include <cxxabi.h>
 #include <map>
 #include <mutex>
+#include <new>
 #include <string>
 #include <sys/mman.h>
 #include <vector>
@@ -34,6 +35,7 @@ std::vector<Launch> g_log;
 std::map<void *, size_t> g_blocks;
 Graph *g_capture = nullptr;
 int g_fail_device = 0, g_fail_host = 0; // the n-th allocation from now on fails
+int g_fail_new = 0;
 int g_last_error = 0;
 size_t g_host_most = 0, g_host_now = 0;
 size_t g_host_limit = ~(size_t)0; // larger pinned allocations fail
@@ -43,6 +45,12 @@ thread_local struct {
     size_t shared;
     void *stream;
 } t_call;
+
+thread_local int t_inside = 0; // allocations of the recorder itself do not count
+struct Inside {
+    Inside() { ++t_inside; }
+    ~Inside() { --t_inside; }
+};
 
 constexpr int INVALID_VALUE = 1, OUT_OF_MEMORY = 2, INVALID_CONFIGURATION = 9;
 
@@ -68,9 +76,25 @@ size_t release(void *p)
 
 } // namespace
 
+// the library's own allocations (it finds these before libstdc++'s)
+void *operator new(size_t bytes)
+{
+    if (!t_inside && g_fail_new > 0 && --g_fail_new == 0) throw std::bad_alloc();
+    if (void *p = std::malloc(bytes ? bytes : 1)) return p;
+    throw std::bad_alloc();
+}
+void *operator new(size_t bytes, const std::nothrow_t &) noexcept
+{
+    if (!t_inside && g_fail_new > 0 && --g_fail_new == 0) return nullptr;
+    return std::malloc(bytes ? bytes : 1);
+}
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
+
 extern "C" {
 
 // ------------------------------------------------------------ the recorder
+void rec_fail_new(int n) { g_fail_new = n; } // the n-th `new` from now on fails
 void rec_reset()
 {
     std::lock_guard<std::mutex> lock(g_mutex);
@@ -127,6 +151,7 @@ int __hipPopCallConfiguration(Dim3 *grid, Dim3 *block, size_t *shared, void **st
 }
 int hipLaunchKernel(const void *f, Dim3 grid, Dim3 block, void **args, size_t, void *)
 {
+    const Inside inside;
     std::lock_guard<std::mutex> lock(g_mutex);
     // what the runtime refuses: no threads, over 1024 a block, 2^32 threads
     // or more along an axis
@@ -149,6 +174,7 @@ int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, int, size
 // ------------------------------------------------------------------ memory
 int hipMalloc(void **p, size_t bytes)
 {
+    const Inside inside;
     std::lock_guard<std::mutex> lock(g_mutex);
     *p = nullptr;
     g_device_sizes.push_back(bytes);
@@ -163,6 +189,7 @@ int hipFree(void *p)
 }
 int hipHostMalloc(void **p, size_t bytes, unsigned)
 {
+    const Inside inside;
     std::lock_guard<std::mutex> lock(g_mutex);
     *p = nullptr;
     if ((g_fail_host > 0 && --g_fail_host == 0) || bytes > g_host_limit) return g_last_error = OUT_OF_MEMORY;
@@ -251,6 +278,7 @@ const char *hipGetErrorString(int e) { return e == OUT_OF_MEMORY ? "out of memor
 // ------------------------------------------------------------------ graphs
 int hipStreamBeginCapture(void *, int)
 {
+    const Inside inside;
     g_capture = new Graph;
     return 0;
 }
@@ -262,6 +290,7 @@ int hipStreamEndCapture(void *, void **graph)
 }
 int hipGraphInstantiate(void **exec, void *graph, void *, char *, size_t)
 {
+    const Inside inside;
     *exec = new Graph(*static_cast<Graph *>(graph));
     return 0;
 }
@@ -277,6 +306,7 @@ int hipGraphExecDestroy(void *exec)
 }
 int hipGraphLaunch(void *exec, void *)
 {
+    const Inside inside;
     const Graph *g = static_cast<Graph *>(exec);
     g_log.insert(g_log.end(), g->launches.begin(), g->launches.end());
     return 0;

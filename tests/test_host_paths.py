@@ -351,3 +351,66 @@ for nx, ny, nz in ((64, 64, 64), (128, 64, 64), (128, 60, 100), (192, 64, 64)):
     assert pair(nx, ny, nz)[0][0] == "k_march3d"
 assert pair(64, 64, 64)[0][0] == pair(100, 84, 92)[0][0] == "k_march3d"
 """)
+
+
+@pytest.mark.parametrize("mask", [False, True])
+def test_out_of_host_memory_is_reported(run, mask):
+    """Whichever host allocation of a first init or of a batch's creation
+    fails: a status and a message, no exception past the C interface, nothing
+    left behind, and the next attempt succeeds."""
+    run(f"""
+m = bytes([1]) + bytes(300 * 200 - 1) if {mask} else None
+h = create(D2Q9, 300, 200, 1, F32, m)
+for k in range(1, 200):
+    R.rec_fail_new(k)
+    rc = L.ptrt_init_equilibrium(h, None, None)
+    R.rec_fail_new(0)
+    if rc == 0:
+        break
+    assert rc == ENOMEM and L.ptrt_last_error(h), (k, rc)
+    assert R.rec_blocks() == 0
+assert rc == 0 and 2 < k < 150, k
+assert set(kernels(h, 10)) == {{"k_tile_2d"}}
+ok(L.ptrt_destroy(h), h)
+assert R.rec_blocks() == 0
+
+sizes = [(40 + k, 30 + k) for k in range(5)]
+for k in range(1, 400):
+    R.rec_fail_new(k)
+    rc, b = batch(sizes, F32)
+    R.rec_fail_new(0)
+    if rc == 0:
+        break
+    assert rc == ENOMEM and not b and L.ptrt_batch_last_error(None), (k, rc)
+    assert R.rec_blocks() == 0, k
+assert rc == 0 and k > 10, k
+L.ptrt_batch_destroy(b)
+""")
+
+
+def test_little_pinned_memory(run):
+    """Where less pinned memory can be had than a transfer asks for, it runs in
+    smaller chunks; none at all is an error that leaves the handle usable."""
+    run("""
+n = 32 * 32 * 32
+rho, u = (C.c_double * n)(*([1.0] * n)), (C.c_double * (3 * n))()
+for limit in (1 << 20, 256 << 10, 64 << 10):
+    h = create(D3Q19, 32, 32, 32)
+    R.rec_limit_host(limit)
+    R.rec_reset()
+    ok(L.ptrt_init_equilibrium(h, rho, u), h)
+    fills = [l for l in launches() if l[0] == "k_init_eq"]
+    assert len(fills) >= (1 << 20) // limit and sum(l[2][0] * 256 for l in fills) >= n
+    R.rec_reset()
+    ok(L.ptrt_moments(h, rho, u), h)
+    assert sum(l[2][0] * 256 for l in launches()) >= n
+    R.rec_limit_host((1 << 64) - 1)
+    ok(L.ptrt_destroy(h), h)
+h = create(D3Q19, 32, 32, 32)
+R.rec_limit_host(1024)
+assert L.ptrt_init_equilibrium(h, rho, u) in (ENOMEM, EDEVICE)
+R.rec_limit_host((1 << 64) - 1)
+ok(L.ptrt_init_equilibrium(h, rho, u), h)
+ok(L.ptrt_destroy(h), h)
+assert R.rec_blocks() == 0
+""")
