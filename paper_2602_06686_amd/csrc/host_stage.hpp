@@ -290,8 +290,13 @@ public:
 private:
     hipError_t open()
     {
-        stage_ = pool_->take((size_t)step_ * per_node_ * (size_t)slots_);
-        if (!stage_.ptr) return hipErrorOutOfMemory;
+        // smaller chunks where no more pinned memory can be had
+        while (!(stage_ = pool_->take((size_t)step_ * per_node_ * (size_t)slots_)).ptr) {
+            if (step_ == 1 || (size_t)step_ * per_node_ <= (32u << 10)) return hipErrorOutOfMemory;
+            step_ = (step_ + 1) / 2;
+            chunks_ = (nodes_ + step_ - 1) / step_;
+            slots_ = (int)std::min<long long>(2, chunks_);
+        }
         for (int k = 0; k < slots_ && chunks_ > 1; ++k) {
             const hipError_t e = hipEventCreateWithFlags(&event_[k], hipEventDisableTiming);
             if (e != hipSuccess) return e;
