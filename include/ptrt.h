@@ -191,17 +191,29 @@ int ptrt_set_forcing(ptrt_ctx *ctx, int forcing);
  * x, PTRT_MODEL_TRT_RLB or PTRT_MODEL_TRT), and
  * - D3Q19 in FP32 or FP64, pairs of steps: nx a multiple of 64 and ny >= 4
  *   (with solid nodes: from 2^24 nodes on, while at most 5 % of the kernel's
- *   column chunks have a solid within one row); with PTRT_MODEL_PTRT also
- *   other nx from 24 on, from 80 000 nodes on, and there with solid nodes
- *   (any nx; in FP32 up to 6 million nodes) in calls of eight steps or more;
+ *   column chunks have a solid within one row);
+ * - D3Q19 in FP32 or FP64 with PTRT_MODEL_PTRT, pairs of steps, by the
+ *   strips of the march: near-equal parts of nx, as few as hold at most 62
+ *   columns each.  Without solid nodes and for other nx: from 80 000 nodes on,
+ *   strips of at least 24 columns (FP32 beyond 1.5 million nodes: 42).  With
+ *   solid nodes, any nx not covered above, in calls of eight steps or more:
+ *   FP64 from 100 000 nodes on (160 000 with several strips), strips of at
+ *   least 24 columns; FP32 from 100 000 nodes on (200 000 with several
+ *   strips) to 6 million, strips of at least 48 columns (56 where there are
+ *   more than three beyond 1.5 million nodes).  A handle that was first
+ *   initialised with another forcing or model keeps one step per pass here
+ *   where ny is odd, or no multiple of the rows that share a layout tile;
  * - D2Q9 in FP32 or FP64, pairs of steps: any size (with solid nodes or open
  *   x: from 2^20 nodes on, while at most 30 % of the rows lie in row chunks
  *   with a solid within one row);
  * - D2Q9 in calls of eight steps or more (any storage type, solid nodes and
  *   open x, PTRT_MODEL_PTRT or _PTRT_EXACT; also PTRT_FORCING_GUO with
  *   periodic x): all but the last one or two steps in passes of up to eight,
- *   then a pass of two steps or a single step.
- * Every other case, and an odd last step, runs one step per pass.  Results
+ *   then a pass of two steps or a single step; long lattices of fewer than
+ *   six rows (twelve in 16 bits) as in shorter calls.
+ * Every other case, and an odd last step, runs one step per pass.  A
+ * divergence check (ptrt_set_divergence_check) splits a call at its steps;
+ * on D2Q9 the pieces then count as calls.  Results
  * are bit-identical either way.  Allowed at any time (waits for the handle's
  * stream). */
 int ptrt_set_steps_per_pass(ptrt_ctx *ctx, int steps);
@@ -209,9 +221,9 @@ int ptrt_set_steps_per_pass(ptrt_ctx *ctx, int steps);
 /* The most recent kernel pass enqueued by ptrt_step: *steps = the steps it
  * covers (1 or 2; 0 before any step; a call that runs in longer passes
  * ends with one of these) and *bytes = its algorithmic HBM
- * traffic in bytes (one step: 2 Q s per node, plus one mask byte per node
- * with solids; two steps: also 2 Q s per node, the state read once by the
- * first step and written once by the second).  For bandwidth accounting;
+ * traffic in bytes (2 Q s per node for either kind, the state read once
+ * by the first step and written once by the last, plus one byte per node
+ * with solids).  For bandwidth accounting;
  * no synchronisation. */
 int ptrt_last_pass(const ptrt_ctx *ctx, int *steps, double *bytes);
 
@@ -399,9 +411,10 @@ int ptrt_batch_autotune(ptrt_batch *b, int *tile_x, int *tile_y, int *blocks, in
 
 /* Enqueue n steps over every instance.  With eight steps or more and two
  * steps per pass (below), all but the last one or two run in passes of up to
- * eight steps on tiles kept in LDS where those are the faster ones, as
- * ptrt_set_steps_per_pass describes for a single lattice, and the call ends
- * with a pass of two steps or a single step.  Otherwise HIP graphs of ten
+ * eight steps on tiles kept in LDS where those are estimated the faster ones
+ * (not with long lattices of few rows or, on large batches, stochastic
+ * rounding), as ptrt_set_steps_per_pass describes for a single lattice, and
+ * the call ends with a pass of two steps or a single step.  Otherwise HIP graphs of ten
  * steps are replayed: pairs of steps as two-step passes, else one launch
  * per step over every instance with the current tile plan.  Asynchronous. */
 int ptrt_batch_step(ptrt_batch *b, int n);

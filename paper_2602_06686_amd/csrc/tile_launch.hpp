@@ -55,9 +55,14 @@ inline int tile_core(int n, int most)
 // lattices and batches (64^2 ... 4096^2, FP32 and FP64): the fastest pass at
 // twelve, within 6 % (700^2) and 2 % of it at the others. The earlier passes
 // take about 2 us a launch and run at 113 (FP32), 64 (FP64) and 180 (16
-// bits) nodes a ns over rows padded to whole strips. For stochastic rounding
-// on large lattices they stay the faster ones: its nine rounded stores double
-// the issue time (2048^2 FP16 23 us against 38).
+// bits) nodes a ns over rows padded to whole strips.  The 16 bits have not
+// been fitted so, and Scheme I and open x use the default forcing's
+// constants: timed on thirteen lattices of 97 x 31 to 4096^2, the passes
+// chosen gained over the earlier ones 1.14 to 2.92 times in FP16 and BF16 (least at
+// 2048^2), 1.08 to 3.0 with Scheme I, open x or walls in FP16, 1.5 to 3.6 in
+// FP32 and FP64. For stochastic rounding on large lattices the earlier passes
+// stay the faster ones: its nine rounded stores double the issue time (2048^2
+// FP16 23 us against 38).
 //
 // Lattices of few rows: a tile is mostly halo, and both estimates are off by
 // up to a quarter, so that long ones take tile passes only if these are
