@@ -166,20 +166,20 @@ private:
 
     HostPool() = default;
 
-    // Whether there are threads for n pieces: up to n - 1, one per megabyte of
-    // the transfers so far and none below 24 MB, so that a handle that is made,
-    // read once and freed does not pay for threads that it hardly uses.
+    // Whether there are threads for n pieces: up to n - 1, one per two megabytes
+    // of the transfers so far and none below 8 MB, so that a handle that is
+    // made, read once and freed does not pay for threads that it hardly uses.
     // Starting and joining one takes 67 us, fifteen 285 us, as long as the
-    // caller alone takes for 1 and 4 MB (made, ten steps, read, freed, us:
-    // 32^3 FP32 388 with pageable copies, 739 with fifteen threads at once;
-    // 64^3 made, one step, read, freed 1050 with threads from 8 MB on, 900 from
-    // 24).  Fewer, or none, where the system refuses.
+    // caller alone takes for 1 and 4 MB into fresh pages (made, one step, read,
+    // freed, us: 56^3 FP32 864 with pageable copies, 646 without threads, 740
+    // with one per 4 MB; 32^3, ten steps, 388, 270 and, with fifteen threads
+    // at once, 739).  Fewer, or none, where the system refuses.
     bool ready(int n)
     {
         std::lock_guard<std::mutex> lock(mutex_);
         const long long mb = moved_ >> 20;
-        if (mb >= 24 && most_ < 0) most_ = std::min(MAX_THREADS, (int)std::thread::hardware_concurrency() - 1);
-        const int want = mb < 24 ? 0 : (int)std::min<long long>(std::min(most_, n - 1), mb);
+        if (mb >= 8 && most_ < 0) most_ = std::min(MAX_THREADS, (int)std::thread::hardware_concurrency() - 1);
+        const int want = mb < 8 ? 0 : (int)std::min<long long>(std::min(most_, n - 1), mb / 2);
         try {
             while (!refused_ && threads_ < want) {
                 thread_[threads_] = std::thread([this] { serve(); });
@@ -228,7 +228,8 @@ public:
     static constexpr int RING = 4;
     // per_node: bytes of one node.  Up to 2 MB in one chunk; more in a ring of
     // the pool's choice, of two chunks at its least size and four beyond, that
-    // overlap.  The host's share, page faults of the caller's fresh arrays
+    // overlap, of 2 MB at least (2.2 MB as two chunks of 1.1: 62 x 1448 read in
+    // a loop 190 us for 150).  The host's share, page faults of the caller's fresh arrays
     // above all, is the longer one, and larger chunks keep more threads busy:
     // 256^3 moments in a sampling loop 17.8 ms with chunks of 8 MB and 8
     // threads, 14.6 with 16 and 16.
@@ -237,7 +238,8 @@ public:
     {
         const long long total = nodes * (long long)per_node, ring = pool->ring_bytes(total);
         const int most = ring == HostPool::LEAST ? 2 : RING;
-        step_ = total <= HostPool::LEAST / 2 ? nodes : std::max(1LL, std::min(ring, total) / most / (long long)per_node);
+        const long long chunk = std::max(HostPool::LEAST / 2, std::min(ring, total) / most);
+        step_ = std::min(nodes, std::max(1LL, chunk / (long long)per_node));
         chunks_ = (nodes + step_ - 1) / step_;
         slots_ = (int)std::min<long long>(most, chunks_);
     }
