@@ -61,7 +61,7 @@ public:
     }
 
     // A transfer of this many bytes begins: the pinned bytes for its ring, about
-    // a twentieth of all transfers so far, from 4 to 64 MB.  Pinned memory that
+    // a tenth of all transfers so far, from 4 to 64 MB.  Pinned memory that
     // is new costs the host 380 us a megabyte in page faults, so that large
     // rings have to be earned: a handle on 64^3 nodes, made, read once and
     // freed, takes 1.1 ms with pageable copies, 2.7 with a ring of 16 MB and
@@ -72,7 +72,7 @@ public:
         std::lock_guard<std::mutex> lock(mutex_);
         moved_ += bytes;
         long long r = LEAST;
-        while (r < MOST && r <= moved_ / 32) r *= 2;
+        while (r < MOST && r <= moved_ / 16) r *= 2;
         return r;
     }
 
