@@ -421,7 +421,9 @@ bool launch_step2_lattice(const StepLaunch &a, double *pass_bytes)
                 // columns run on one XCD (the counters give the HBM reads)
                 if (pass_bytes) *pass_bytes = 2.0 * a.g.nx * a.g.ny * a.g.nz * L::Q * sizeof(S);
                 const Coef<L, C> r = make_coef<L, C>(a.tau_plus, a.Lambda, a.force);
-                // per-task source offsets where the layout allows (FP32)
+                // per-task source offsets where the layout allows (FP32): not
+                // in planes of 4 GiB, nor at ragged ny after a first init with
+                // a forcing or model of one step per pass
                 const bool zoff = step2_zoff_ok<S>(a.g);
                 auto with_zoff = [&](auto f) {
                     if constexpr (sizeof(S) == 4) {

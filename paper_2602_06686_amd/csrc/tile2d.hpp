@@ -22,10 +22,11 @@
 //
 // What bounds it and why this shape: instruction issue.  A wave updates a
 // row of 64 nodes with about 105 VALU instructions, 9 LDS reads and 9 LDS
-// writes with compile-time offsets from one address register (VALU busy
-// 94 % of the time at 2048^2 in FP32, 48 % in FP64, whose registers leave
-// four waves per SIMD); HBM sees the state once per pass.  Two
-// workgroups per CU, one computing while the other waits for its first
+// writes with compile-time offsets from one address register.  At 2048^2 the
+// SIMDs spend as many quads of clocks on VALU instructions as a pass takes in
+// FP32 (107 % of the busy clocks), 77 % of them in FP64, whose registers
+// leave four waves per SIMD; HBM moves 1.05 times the state in and out per
+// pass (FP64 1.18: halos of narrower regions).  Two workgroups per CU, one computing while the other waits for its first
 // step's loads.  Measured against the passes of two steps along rows
 // (k_step2_2d; us a step, before -> after): 2048^2 FP32 36.7 -> 17.7,
 // FP64 64.8 -> 36.5; 4096^2 FP32 156 -> 71, FP16 (one step a pass before)
