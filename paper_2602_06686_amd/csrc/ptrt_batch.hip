@@ -500,7 +500,7 @@ int build_tile_tasks(ptrt_batch *b, const uint8_t *mask)
     std::vector<std::pair<int, int>> sizes;
     for (const HostInst &h : b->inst) sizes.emplace_back(h.nx, h.ny);
     const TilePlan p = choose_tile_plan(b->storage, sizes);
-    if (p.shape == TILE_NONE) return PTRT_OK;
+    if (p.shape == TILE_NONE || p.thin) return PTRT_OK;
     std::vector<int4> tasks;
     for (int k = 0; k < b->count; ++k) {
         const HostInst &h = b->inst[k];

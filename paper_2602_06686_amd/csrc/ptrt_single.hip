@@ -793,8 +793,12 @@ int launch_check(ptrt_ctx *c)
 // D2Q9 with the default forcing or, on periodic lattices, Scheme I.
 bool tiles_apply(const ptrt_ctx *c, int n)
 {
+    // where shorter calls take passes of two steps but for these
+    const bool single = storage_bytes(c->storage) > 2 &&
+                        (c->forcing == FORCE_GUO || (c->open && c->N < TWO_STEP_SPECIAL_NODES));
     return n >= TILE_MIN_STEPS && c->steps_per_pass == 2 && c->tile.shape != TILE_NONE &&
            (c->model == MODEL_PTRT || c->model == MODEL_PTRT_EXACT) &&
+           (!c->tile.thin || single) &&
            (c->forcing == FORCE_II || (c->forcing == FORCE_GUO && !c->open));
 }
 

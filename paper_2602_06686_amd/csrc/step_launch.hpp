@@ -314,6 +314,10 @@ void launch_march(const StepLaunch &a, double *pass_bytes)
     go(MarchShape<S, 6>{}, std::false_type{});
 }
 
+// D2Q9 lattices with solids or open x take two steps per pass from here on
+// (measured: in launch_step2_lattice).
+constexpr long long TWO_STEP_SPECIAL_NODES = 1LL << 20;
+
 template <class L>
 bool launch_step2_lattice(const StepLaunch &a, double *pass_bytes)
 {
@@ -339,7 +343,7 @@ bool launch_step2_lattice(const StepLaunch &a, double *pass_bytes)
         // with open x (inlet / outlet strips in the special launch), the
         // same floor (measured on the 1050^2 square cylinder, below)
         if (a.has_mask || a.open) {
-            if ((long long)a.g.nx * a.g.ny < (1LL << 20)) return false;
+            if ((long long)a.g.nx * a.g.ny < TWO_STEP_SPECIAL_NODES) return false;
             if (!a.tasks_plain || !a.tasks_special || a.n_plain + a.n_special == 0) return false;
             if (a.masked_rows > 0.3 * a.g.ny) return false;
         }

@@ -30,6 +30,7 @@ inline void with_tile_shape(int shape, F &&f)
 
 struct TilePlan {
     int shape = TILE_NONE; // none: no tile passes on this lattice
+    bool thin = false;     // not against passes of two steps (few rows, below)
     int T = 0;             // steps of a full pass
     int cw = 0, ch = 0;    // core of a single lattice's tiles
     int tiles_x = 0, tiles = 0;
@@ -72,7 +73,10 @@ inline int tile_core(int n, int most)
 // 4.07, 100000 x 3 FP64 5.65 -> 7.81, 1000000 x 6 FP16 34.0 -> 46.9, 1000
 // lattices of 200 x 4 and 5 FP64 14.9 -> 18.2). In 16 bits a batch's earlier
 // pass is slower and the tile passes gain there (13.1 -> 10.7), so that only
-// long rows count.
+// long rows count.  With Scheme I, and with open x below 2^20 nodes, the
+// earlier pass of 32 and 64 bits is one of a single step, and the tile passes
+// gain as estimated (100000 x 5 with open x FP32 7.98 -> 5.20, FP64 12.8 ->
+// 9.5): TilePlan::thin marks a plan that is for these only.
 inline TilePlan choose_tile_plan(int storage, const std::vector<std::pair<int, int>> &sizes)
 {
     const size_t elem = storage_bytes(storage);
@@ -102,7 +106,8 @@ inline TilePlan choose_tile_plan(int storage, const std::vector<std::pair<int, i
     const bool few_rows =
         columns > (half && rows > 1 ? 99999.0 : 50000.0) && thin > (f64 ? 0.5 : 0.75) * nodes;
     TilePlan best;
-    double best_cost = (2.0 + padded / earlier_rate) * (few_rows ? (f64 ? 0.75 : 0.8) : 1.0);
+    const double earlier = 2.0 + padded / earlier_rate;
+    double best_cost = earlier;
     for (int shape = 0; shape < TILE_SHAPES; ++shape) {
         with_tile_shape(shape, [&](auto sh) {
             using SH = decltype(sh);
@@ -149,6 +154,7 @@ inline TilePlan choose_tile_plan(int storage, const std::vector<std::pair<int, i
             }
         });
     }
+    best.thin = few_rows && best_cost > earlier * (f64 ? 0.75 : 0.8);
     return best;
 }
 

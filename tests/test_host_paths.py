@@ -199,9 +199,12 @@ def test_few_rows_keep_the_earlier_passes(run):
     mostly halo take the passes of one and two steps; short ones, those of
     more rows and 16-bit batches take tile passes."""
     run("""
-def kind(nx, ny, storage):
+def kind(nx, ny, storage, open_x=False, forcing=0):
     h = create(D2Q9, nx, ny, 1, storage)
+    if open_x:
+        ok(L.ptrt_set_open_x(h, C.c_double(0.01), C.c_double(1.0)), h)
     init(h)
+    ok(L.ptrt_set_forcing(h, forcing), h)
     k = set(kernels(h, 10))
     ok(L.ptrt_destroy(h), h)
     assert len(k) == 1, k
@@ -215,6 +218,11 @@ for storage, few, earlier in ((F32, 6, "k_step2_2d"), (F64, 6, "k_step2_2d"), (F
     for nx, ny in ((100, 1), (10000, 1), (10000, 3), (1000000, 16), (7, 200000), (509, 381)):
         assert kind(nx, ny, storage) == "k_tile_2d", (nx, ny, storage)
 assert kind(70000, 4, F32) == kind(1000000, 8, F32) == "k_tile_2d"
+# the earlier pass of open x and of Scheme I is one of a single step
+for storage in (F32, F64):
+    assert kind(100000, 3, storage, open_x=True) == kind(100000, 3, storage, forcing=2) == "k_tile_2d"
+    assert kind(1000000, 4, storage, open_x=True) == "k_step2_2d"
+assert kind(1000000, 10, F16, open_x=True) == kind(1000000, 10, F16, forcing=2) == "k_step"
 
 def batch_kind(sizes, storage):
     rc, b = batch(sizes, storage)
