@@ -195,14 +195,18 @@ int ptrt_set_forcing(ptrt_ctx *ctx, int forcing);
  * - D3Q19 in FP32 or FP64 with PTRT_MODEL_PTRT, pairs of steps, by the
  *   strips of the march: near-equal parts of nx, as few as hold at most 62
  *   columns each.  Without solid nodes and for other nx: from 80 000 nodes on,
- *   strips of at least 24 columns (FP32 beyond 1.5 million nodes: 42).  With
- *   solid nodes, any nx not covered above, in calls of eight steps or more:
- *   FP64 from 100 000 nodes on (160 000 with several strips), strips of at
+ *   strips of at least 24 columns (FP32 beyond 1.5 million nodes: 42), not
+ *   with ny of 1, 3, 4, 7 or 8 (FP32: 1, 7 or 8), nor in FP64 with nz 1 and
+ *   several strips.  With solid nodes, any nx not covered
+ *   above, in calls of eight steps or more: FP64 from 100 000 nodes on (160
+ *   000 and nz of 3 with several strips), strips of at
  *   least 24 columns; FP32 from 100 000 nodes on (200 000 with several
  *   strips) to 6 million, strips of at least 48 columns (56 where there are
- *   more than three beyond 1.5 million nodes).  A handle that was first
- *   initialised with another forcing or model keeps one step per pass here
- *   where ny is odd, or no multiple of the rows that share a layout tile;
+ *   more than three beyond 1.5 million nodes); with ny below 24 only where
+ *   few of a workgroup's rows stay empty, and in FP32 only in one strip.  A
+ *   handle that was first initialised with another forcing or model keeps
+ *   one step per pass here where ny is odd, or no multiple of the rows that
+ *   share a layout tile;
  * - D2Q9 in FP32 or FP64, pairs of steps: any size (with solid nodes or open
  *   x: from 2^20 nodes on, while at most 30 % of the rows lie in row chunks
  *   with a solid within one row);

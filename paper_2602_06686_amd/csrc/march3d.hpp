@@ -72,7 +72,7 @@ struct MarchShape {
     static constexpr int PAD = W; // sources of the garbage lanes 0 and 63
     static constexpr int elems = K::planes * AP + 2 * PAD;
     template <class T>
-    static constexpr int waves_per_simd = sizeof(T) == 8 ? 2 : (BY == 6 ? 4 : 3);
+    static constexpr int waves_per_simd = sizeof(T) == 8 ? 2 : (BY == 4 ? 3 : 4);
 };
 
 template <class S, class SH, bool SOLID>

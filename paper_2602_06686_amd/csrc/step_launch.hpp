@@ -200,16 +200,23 @@ constexpr int MARCH_SOLID_MIN_STEPS = 8;
 // lanes: at least 24 columns, and in FP32 at least 42 once the lattice is
 // too large for the last-level cache to hide the others' loads (130^3, 44
 // columns, 67.4 -> 65.5; 24 to 42 columns: 24 x 100 x 102 FP32 10.3 -> 10.0,
-// FP64 15.7 -> 15.2, 32 x 200 x 150 23.6 -> 19.8, 54.3 -> 47.6).  With solids
+// FP64 15.7 -> 15.2, 32 x 200 x 150 23.6 -> 19.8, 54.3 -> 47.6), or one row,
+// or three to eight, leave most of a workgroup's empty (125 x 1 x 1000 FP64
+// 9.0 -> 23.0, 125 x 7 x 300 14.0 -> 16.9, FP32 9.5 -> 10.0), or in FP64
+// several strips have one plane, with two of first steps beside it (300 x
+// 1000 x 1 15.7 -> 20.1; with solids two planes 12.4 -> 14.8).  With solids
 // (walls or a block over 1/8 of each axis; one step per pass before) it is
 // faster with at least 24 columns in FP64 (24 x 100 x 102 17.4 -> 12.9, 128
 // x 96 x 96 62.9 -> 49.7, 200^3 471 -> 319, 256^3 854 -> 614; 32 columns
 // within 2 % either way), and in FP32 with rows mostly full and below 6
 // million nodes (50 x 100 x 102 17.9 -> 13.9, 100 x 84 x 92 23.8 -> 19.6,
 // 180 x 150 x 150 128 -> 103).  Small lattices, whose one step is a launch and
-// little more, and in FP32 four strips or more beyond 1.5 million nodes keep
-// one step per pass (FP32 60 x 40 x 40 6.0 -> 6.7, 100 x 40 x 40 7.5 -> 8.5,
-// 200 x 100 x 102 58.4 -> 62.0; FP64 64 x 40 x 40 8.1 -> 8.8).
+// little more, fewer than 24 rows that leave those of a workgroup a fifth
+// empty (FP32 in several strips at any rate), and in FP32 four strips or more
+// beyond 1.5 million nodes keep one step per pass (FP32 60 x 40 x 40 6.0 ->
+// 6.7, 100 x 40 x 40 7.5 -> 8.5, 96 x 16 x 180 9.5 -> 10.5, 200 x 100 x 102
+// 58.4 -> 62.0; FP64 64 x 40 x 40 8.1 -> 8.8, 96 x 8 x 220 10.5 -> 11.7, 64 x
+// 16 x 180 10.7 -> 13.4; but 96 x 12 x 220 13.9 -> 11.8).
 inline bool march_lattice(const Geom &g, int storage, bool solids)
 {
     if (storage != PTRT_F32 && storage != PTRT_F64) return false;
@@ -219,11 +226,20 @@ inline bool march_lattice(const Geom &g, int storage, bool solids)
         return false;
     const double nodes = (double)g.nx * g.ny * g.nz;
     const int cols = march_cols(g.nx), strips = (g.nx + cols - 1) / cols;
+    if (!solids && g.nx % Step2Shape<D3Q19, float>::BX == 0 && g.ny >= Step2Shape<D3Q19, float>::BY)
+        return nodes < 8e5;
+    if (elem == 8 && strips > 1 && g.nz <= (solids ? 2 : 1)) return false;
+    // few rows: how well they fill those of the workgroups
+    auto filled = [&](int rows) { return (double)g.ny / ((g.ny + rows - 1) / rows * rows); };
+    if (g.ny == 1 || (!solids && g.ny > (elem == 8 ? 2 : 4) && g.ny < 10 && filled(6) < 0.7)) return false;
+    if (solids && g.ny < 24) {
+        const double fill = elem == 8 && (cols <= 40 || filled(14) > 0.95) ? filled(14) : filled(6);
+        if (strips > 1 ? elem == 4 || fill < 0.8 : fill < 0.7) return false;
+    }
     if (solids && elem == 8) return nodes >= (strips > 1 ? 1.6e5 : 1e5) && cols >= 24;
     if (solids)
         return nodes >= (strips > 1 ? 2e5 : 1e5) && nodes <= 6e6 &&
                cols >= (strips > 3 && nodes > 1.5e6 ? 56 : 48);
-    if (g.nx % Step2Shape<D3Q19, float>::BX == 0 && g.ny >= Step2Shape<D3Q19, float>::BY) return nodes < 8e5;
     return nodes >= 8e4 && cols >= (elem == 4 && nodes > 1.5e6 ? 42 : 24);
 }
 
@@ -299,6 +315,13 @@ void launch_march(const StepLaunch &a, double *pass_bytes)
             }
         }
         go(MarchShape<S, 6>{}, std::true_type{});
+        return;
+    }
+    // two rows (us a step, one step per pass / six rows / two: 125 x 2 x 600
+    // FP32 8.3 / 9.7 / 6.2, FP64 10.1 / 16.7 / 10.0; 300 x 2 x 200 7.4 / 6.5 /
+    // 4.7, 10.0 / 10.4 / 7.1)
+    if (a.g.ny == 2) {
+        go(MarchShape<S, 2>{}, std::false_type{});
         return;
     }
     // six rows share their halo better; on large FP32 lattices more rows in

@@ -422,3 +422,36 @@ ok(L.ptrt_init_equilibrium(h, rho, u), h)
 ok(L.ptrt_destroy(h), h)
 assert R.rec_blocks() == 0
 """)
+
+
+def test_where_solids_take_the_march(run):
+    """Sizes on both sides of the rule for D3Q19 with solids: columns, nodes,
+    strips, few rows."""
+    run("""
+def kind(nx, ny, nz, storage, solids=True):
+    h = create(D3Q19, nx, ny, nz, storage, bytes([1]) + bytes(nx * ny * nz - 1) if solids else None)
+    init(h)
+    k = set(kernels(h, 8))
+    ok(L.ptrt_destroy(h), h)
+    assert len(k) == 1, k
+    return k.pop() == "k_march3d"
+
+for size in ((24, 100, 102), (50, 50, 40), (64, 50, 64), (96, 12, 220), (126, 14, 200), (48, 45, 47)):
+    assert kind(*size, F64), size
+for size in ((23, 100, 102), (56, 40, 40), (64, 40, 40), (96, 8, 220), (64, 16, 180), (96, 13, 220)):
+    assert not kind(*size, F64), size
+for size in ((48, 45, 47), (50, 14, 200), (100, 84, 92), (180, 150, 150), (145, 150, 150)):
+    assert kind(*size, F32), size
+for size in ((47, 60, 61), (60, 40, 40), (100, 40, 40), (96, 16, 180), (200, 100, 102), (128, 96, 96), (180, 190, 180)):
+    assert not kind(*size, F32), size
+for storage in (F16, BF16):
+    assert not kind(100, 84, 92, storage)
+# without solids: few rows and planes
+for size in ((125, 2, 600), (200, 5, 300), (125, 6, 300), (200, 10, 200), (62, 1500, 1), (300, 1000, 2)):
+    assert kind(*size, F64, False) and kind(*size, F32, False), size
+for size in ((125, 1, 1000), (125, 7, 300), (200, 8, 220)):
+    assert not kind(*size, F64, False) and not kind(*size, F32, False), size
+for size in ((300, 1000, 1), (125, 4, 600)):
+    assert not kind(*size, F64, False) and kind(*size, F32, False), size
+assert not kind(100, 1000, 2, F64) and kind(100, 1000, 2, F32)
+""")
